@@ -8,40 +8,51 @@ namespace nd {
 
 
 // ------------------------------------------------------------------ models
+// Flip the sign of v where bit 31 of m is set.
+__device__ __forceinline__ double flip_sign(double v, uint32_t m) {
+    return __longlong_as_double(__double_as_longlong(v) ^ ((long long)(m & 0x80000000u) << 32));
+}
+
 // sin and cos of one double: Cody-Waite reduction by pi/2 (two-part constant,
-// each part subtracted with one fused multiply-add), then the Taylor series of
-// sin and cos on [-pi/4, pi/4] up to degrees 15 and 16 (truncation below 5e-17)
-// evaluated by Horner in r^2, and the quadrant swap.  The reduced argument
-// carries the rounding of the first subtraction (up to half an ulp of r, about
-// 5.5e-17 near pi/4) and the neglected third part of pi/2 (grows with |x|);
-// measured against glibc over 1.6e7 arguments up to 3e13 the largest absolute
-// error was 1.1e-16.  Inf and NaN give NaN.
+// each part subtracted with one fused multiply-add), then minimax polynomials of
+// sin and cos on [-pi/4, pi/4] of degrees 13 and 14 (fitted by the Remez
+// exchange on (sin r - r)/r^3 and (cos r - 1 + r^2/2)/r^4, coefficients rounded
+// one after the other; approximation error 1.6e-18 and 4.8e-20) by Horner in
+// r^2, and the quadrant swap.  The quadrant q mod 4 is read from the bits of
+// frac(q / 4), which is 0, 1/4, 1/2 or 3/4 for any integer q: high words 0,
+// 0x3fd00000, 0x3fe00000 and 0x3fe80000, so bits 19 and 20 give the swap, bit 21
+// the sign of the sine and bit 21 after adding 0x180000 that of the cosine.
+// The reduced argument carries the rounding of the first subtraction (up to
+// half an ulp of r, about 5.5e-17 near pi/4) and the neglected third part of pi/2
+// (grows with |x|); over 6e6 arguments up to 3e13 the largest error against
+// 113-bit values was 1.30e-16 and the rms error 3.17e-17 (Taylor series of two
+// degrees more: 1.44e-16 and 3.20e-17).  Bound: FP64 issue of the callers; this
+// form takes 20 FP64 operations, the Taylor form with the quadrant by floor and
+// conversion took 24.  Inf and NaN give NaN.
 __device__ __forceinline__ void sincos_cw(double x, double* sp, double* cp) {
     const double q = rint(x * 0.63661977236758134308);          // x / (pi/2), nearest
     const double r1 = fma(-q, 1.5707963267948966192, x);        // pi/2 rounded to double
     const double r = fma(-q, 6.123233995736766036e-17, r1);     // pi/2 minus that
     const double r2 = r * r;
-    double ps = -1.0 / 1307674368000.0;                          // -1/15!
-    ps = fma(ps, r2, 1.0 / 6227020800.0);
-    ps = fma(ps, r2, -1.0 / 39916800.0);
-    ps = fma(ps, r2, 1.0 / 362880.0);
-    ps = fma(ps, r2, -1.0 / 5040.0);
-    ps = fma(ps, r2, 1.0 / 120.0);
-    ps = fma(ps, r2, -1.0 / 6.0);
+    double ps = 1.588805743874414e-10;
+    ps = fma(ps, r2, -2.5050590858861764e-08);
+    ps = fma(ps, r2, 2.7557312482336066e-06);
+    ps = fma(ps, r2, -0.00019841269825742673);
+    ps = fma(ps, r2, 0.008333333333316218);
+    ps = fma(ps, r2, -0.166666666666666);
     const double sn = fma(r * r2, ps, r);
-    double pc = 1.0 / 20922789888000.0;                          // 1/16!
-    pc = fma(pc, r2, -1.0 / 87178291200.0);
-    pc = fma(pc, r2, 1.0 / 479001600.0);
-    pc = fma(pc, r2, -1.0 / 3628800.0);
-    pc = fma(pc, r2, 1.0 / 40320.0);
-    pc = fma(pc, r2, -1.0 / 720.0);
-    pc = fma(pc, r2, 1.0 / 24.0);
+    double pc = -1.1359934247561652e-11;
+    pc = fma(pc, r2, 2.087572928127532e-09);
+    pc = fma(pc, r2, -2.75573144010307e-07);
+    pc = fma(pc, r2, 2.4801587289671537e-05);
+    pc = fma(pc, r2, -0.0013888888888874474);
+    pc = fma(pc, r2, 0.0416666666666666);
     pc = fma(pc, r2, -0.5);
     const double cs = fma(r2, pc, 1.0);
-    const int k = (int)(q - 4.0 * floor(q * 0.25));  // quadrant q mod 4, exact for any integer q  // two's complement: also right for negative q
-    const double s0 = (k & 1) ? cs : sn, c0 = (k & 1) ? sn : cs;
-    *sp = (k & 2) ? -s0 : s0;
-    *cp = ((k + 1) & 2) ? -c0 : c0;
+    const uint32_t f = (uint32_t)((unsigned long long)__double_as_longlong(__builtin_amdgcn_fract(q * 0.25)) >> 32);
+    const bool swap = (f & 0x180000u) != 0;
+    *sp = flip_sign(swap ? cs : sn, f << 10);
+    *cp = flip_sign(swap ? sn : cs, (f + 0x180000u) << 10);
 }
 
 template <int MODEL, class KT>
@@ -74,9 +85,9 @@ struct RingModel<ND_KURAMOTO, KT> {
                                                double* k) {
         (void)z;
         if constexpr (sizeof(KT) == 8) {
-            const double ca = xo.x * d.p[2] - xo.y * d.p[3];
-            const double sa = xo.y * d.p[2] + xo.x * d.p[3];
-            k[0] = d.p[0] + d.p[1] * (ca * W.y - sa * W.x);
+            const double ca = fma(xo.x, d.p[2], -(xo.y * d.p[3]));
+            const double sa = fma(xo.y, d.p[2], xo.x * d.p[3]);
+            k[0] = fma(d.p[1], fma(ca, W.y, -(sa * W.x)), d.p[0]);
         } else {
             const float cf = (float)xo.x, sf = (float)xo.y;
             const float ca = cf * (float)d.p[2] - sf * (float)d.p[3];
@@ -126,10 +137,11 @@ struct RingModel<ND_FHN, KT> {
         const double Du = W.x - d.p[5] * u;
         const double Dv = W.y - d.p[5] * v;
         if constexpr (sizeof(KT) == 8) {
-            const double cu = d.p[2] * (d.p[3] * Du + d.p[4] * Dv);
-            const double cv = d.p[2] * (d.p[3] * Dv - d.p[4] * Du);
-            k[0] = (u - u * u * u * (1.0 / 3.0) - v + cu) * d.p[6];
-            k[1] = u + d.p[1] + cv;
+            const double cu = fma(d.p[3], Du, d.p[4] * Dv);
+            const double cv = fma(d.p[3], Dv, -(d.p[4] * Du));
+            const double cubic = fma(u * u * u, -1.0 / 3.0, u);
+            k[0] = fma(d.p[2], cu, cubic - v) * d.p[6];
+            k[1] = fma(d.p[2], cv, u + d.p[1]);
         } else {
             const float uf = (float)u, vf = (float)v, duf = (float)Du, dvf = (float)Dv;
             const float kap = (float)d.p[2], cph = (float)d.p[3], sph = (float)d.p[4];
