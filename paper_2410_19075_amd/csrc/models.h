@@ -55,6 +55,16 @@ __device__ __forceinline__ void sincos_cw(double x, double* sp, double* cp) {
     *cp = flip_sign(swap ? sn : cs, (f + 0x180000u) << 10);
 }
 
+// The descriptor fields of a step loop that stays in one workgroup.
+struct ModelConst {
+    double p[7], dt3, dt6;
+    __device__ __forceinline__ explicit ModelConst(const NetDesc& d) : dt3(d.dt3), dt6(d.dt6) {
+#pragma unroll
+        for (int q = 0; q < 7; ++q) p[q] = d.p[q];
+    }
+};
+
+// The right-hand sides read the model constants as d.p[], d a NetDesc or a ModelConst.
 template <int MODEL, class KT>
 struct RingModel;
 
@@ -81,8 +91,8 @@ struct RingModel<ND_KURAMOTO, KT> {
         }
         return make_double2(c, s);
     }
-    __device__ static __forceinline__ void rhs(const NetDesc& d, const double* z, double2 xo, double2 W,
-                                               double* k) {
+    template <class D>
+    __device__ static __forceinline__ void rhs(const D& d, const double* z, double2 xo, double2 W, double* k) {
         (void)z;
         if constexpr (sizeof(KT) == 8) {
             const double ca = fma(xo.x, d.p[2], -(xo.y * d.p[3]));
@@ -105,8 +115,8 @@ template <class KT>
 struct RingModel<ND_KURAMOTO_INERTIA, KT> {
     static constexpr int V = 2;
     __device__ static __forceinline__ double2 map(const double* z) { return RingModel<ND_KURAMOTO, KT>::map(z); }
-    __device__ static __forceinline__ void rhs(const NetDesc& d, const double* z, double2 xo, double2 W,
-                                               double* k) {
+    template <class D>
+    __device__ static __forceinline__ void rhs(const D& d, const double* z, double2 xo, double2 W, double* k) {
         double force[1];
         RingModel<ND_KURAMOTO, KT>::rhs(d, z, xo, W, force);  // omega + coupling, as first-order Kuramoto
         k[0] = z[1];
@@ -130,8 +140,8 @@ template <class KT>
 struct RingModel<ND_FHN, KT> {
     static constexpr int V = 2;
     __device__ static __forceinline__ double2 map(const double* z) { return make_double2(z[0], z[1]); }
-    __device__ static __forceinline__ void rhs(const NetDesc& d, const double* z, double2 xo, double2 W,
-                                               double* k) {
+    template <class D>
+    __device__ static __forceinline__ void rhs(const D& d, const double* z, double2 xo, double2 W, double* k) {
         (void)xo;
         const double u = z[0], v = z[1];
         const double Du = W.x - d.p[5] * u;

@@ -224,6 +224,31 @@ __device__ __forceinline__ void block_sum_and_exscan(double (&r)[NR], double (&s
     lds_barrier();
 }
 
+// Sum of the first `wid` of NW (<= 16) wave totals in LDS: every lane takes one
+// total, a row-wide DPP scan adds them in a fixed tree, and the value before
+// `wid` (uniform) is broadcast.
+template <int NW>
+__device__ __forceinline__ double2 waves_before(const double2* wtot, int wid) {
+    static_assert(NW <= 16, "one DPP row");
+    double2 v = wtot[threadIdx.x & (NW - 1)];
+    v.x += dpp_move<0x111>(v.x);  // row_shr:1
+    v.y += dpp_move<0x111>(v.y);
+    if constexpr (NW > 2) {
+        v.x += dpp_move<0x112>(v.x);
+        v.y += dpp_move<0x112>(v.y);
+    }
+    if constexpr (NW > 4) {
+        v.x += dpp_move<0x114>(v.x);
+        v.y += dpp_move<0x114>(v.y);
+    }
+    if constexpr (NW > 8) {
+        v.x += dpp_move<0x118>(v.x);
+        v.y += dpp_move<0x118>(v.y);
+    }
+    if (wid == 0) return make_double2(0.0, 0.0);
+    return make_double2(wave_bcast(v.x, wid - 1), wave_bcast(v.y, wid - 1));
+}
+
 // Block-exclusive prefix (thread order) of NS values, in every thread: the scan
 // half of block_sum_and_exscan, for callers with no block sums to take along.
 // lds: NS * (BS/64) doubles.

@@ -322,31 +322,49 @@ __global__ __launch_bounds__(BS) void k_ring_stage(const NetDesc* __restrict__ D
 // registers for a whole chunk of steps.  Per stage the mapped values are
 // prefix-summed in LDS (double) and every window sum is a difference of two
 // prefix values (wrapping through the ring total); no global memory traffic
-// between stages.  Each thread owns EPT consecutive elements.  The prefix
-// array holds element k at k + k / EPT, so the lanes' stride-EPT accesses land
-// on distinct LDS banks (stride EPT + 1 doubles, at any offset).
+// between stages.  Each thread owns EPT consecutive elements.
+// Bound: FP64 issue (about 85 vector instructions per element and stage) and,
+// with few rings per CU, the chain map - scan - barrier - prefix - barrier -
+// windows.  So a stage has two barriers (the wave totals, the prefix array), the
+// thread-local prefixes stay in registers until the prefix is written once, both
+// components travel in one 16-byte LDS access, and the window ends are fixed
+// LDS offsets computed before the step loop, with the ring total added by a
+// select where the window wraps (no divergent branches).  The prefix array holds
+// prefix k at k + k / EPT, so the lanes' stride is EPT + 1 16-byte entries: odd,
+// hence free of bank conflicts.  Measured per stage (one 1024-ring / 512 rings /
+// 4096 rings, Kuramoto FP64): 0.93 / 1.67 / 9.7 us; with four barriers, the
+// prefix rewritten in LDS and branches on the wrap 1.95 / 2.63 / 12.9 us.
 template <int MODEL, class KT, int BS, int EPT, bool MV>
 __global__ __launch_bounds__(BS) void k_ring_resident(const NetDesc* __restrict__ D, const int2* __restrict__ work,
                                                       const int* __restrict__ nwork_p, int chunk) {
     using M = RingModel<MODEL, KT>;
-    constexpr int V = M::V, T = BS * EPT, NW = BS / kWave, TP = T + BS;
-    auto px = [](int k) { return k + k / EPT; };  // padded position of element k
-    extern __shared__ double pf[];  // [2][TP]: inclusive prefix sums of the two map components (padded)
-    __shared__ double lds[8 * NW];
+    constexpr int V = M::V, NW = BS / kWave;
+    // byte offset of prefix k (elements before k), k = 0 .. BS*EPT
+    auto px = [](int k) { return (k + k / EPT) * (int)sizeof(double2); };
+    extern __shared__ char pf[];
+    auto pre = [&](int off) -> double2& { return *(double2*)(pf + off); };
+    __shared__ double2 wtot[NW];
+    __shared__ double lds[4 * NW];
     const int nwork = *nwork_p;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), i0 = tid * EPT;
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
         const int2 wk = work[w];
         const NetDesc& d = D[wk.x];
         if (d.nsteps <= 0) continue;
+        const ModelConst mc(d);  // read once: through d they were scalar loads in every stage
         const int steps = (int)min((int64_t)chunk, d.nsteps);
         const int n = (int)d.n, P = (int)d.P;
         const double dt = d.dt;
+        const bool act = wid * kWave * EPT < n;  // waves without elements only join the barriers
         const ND_GLOBAL double* yin = gp(d.y[d.ypar]);
         double y[EPT][V], acc[EPT][V], kp[EPT][V], dth[EPT];
+        // window [i-P, i+P] = prefix(hi) - prefix(lo), plus the ring total where it wraps
+        int hi[EPT], lo[EPT];
+        bool wrap[EPT];
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
-            const int i = tid * EPT + e;
+            const int i = i0 + e;
 #pragma unroll
             for (int v = 0; v < V; ++v) {
                 y[e][v] = i < n ? yin[(int64_t)v * n + i] : 0.0;
@@ -354,85 +372,99 @@ __global__ __launch_bounds__(BS) void k_ring_resident(const NetDesc* __restrict_
                 kp[e][v] = 0.0;
             }
             dth[e] = 0.0;
+            int h = i + P + 1, l = i - P;
+            wrap[e] = l < 0 || h > n;
+            if (l < 0) l += n;
+            if (h > n) h -= n;
+            hi[e] = px(i < n ? h : 0);
+            lo[e] = px(i < n ? l : 0);
         }
+        if (tid == 0) pre(0) = make_double2(0.0, 0.0);
+        if (!act && lane == 0) wtot[wid] = make_double2(0.0, 0.0);
+        const int rtot = px(n);
+        // next run step at which R is recorded
+        int64_t rk = (d.g0 + d.r_every - 1) / d.r_every;
+        int64_t rg = (d.obs & OBS_R) ? rk * d.r_every - d.g0 : steps;  // relative to g0
         for (int j = 0; j < steps; ++j) {
-            const int64_t g = d.g0 + j;
+            const bool rec = j == rg;
 #pragma unroll
             for (int s = 1; s <= 4; ++s) {
                 const double cdt = s == 4 ? dt : 0.5 * dt;
                 double z[EPT][V];
-                double2 x[EPT];
-                double tot[2] = {0.0, 0.0};
-                double ru[2] = {0.0, 0.0};  // FHN: unit phase vectors for R
+                double2 x[EPT], in[EPT];  // mapped values, thread-local inclusive prefixes
+                double2 ex = make_double2(0.0, 0.0);
+                if (act) {
+                    double2 tot = make_double2(0.0, 0.0);
 #pragma unroll
-                for (int e = 0; e < EPT; ++e) {
-                    const int i = tid * EPT + e;
+                    for (int e = 0; e < EPT; ++e) {
 #pragma unroll
-                    for (int v = 0; v < V; ++v) z[e][v] = s == 1 ? y[e][v] : fma(cdt, kp[e][v], y[e][v]);
-                    x[e] = M::map(z[e]);
-                    if (i >= n) x[e] = make_double2(0.0, 0.0);
-                    tot[0] += x[e].x;
-                    tot[1] += x[e].y;
-                    // thread-local inclusive prefix, completed below with the
-                    // block-exclusive offset of this thread
-                    pf[px(tid * EPT + e)] = tot[0];
-                    pf[TP + px(tid * EPT + e)] = tot[1];
-                    if constexpr (MODEL == ND_FHN) {
-                        if (s == 1 && i < n) {
-                            const double r = sqrt(z[e][0] * z[e][0] + z[e][1] * z[e][1]);
-                            ru[0] += z[e][0] / r;
-                            ru[1] += z[e][1] / r;
+                        for (int v = 0; v < V; ++v) z[e][v] = s == 1 ? y[e][v] : fma(cdt, kp[e][v], y[e][v]);
+                        x[e] = M::map(z[e]);
+                        if (i0 + e >= n) x[e] = make_double2(0.0, 0.0);
+                        tot.x += x[e].x;
+                        tot.y += x[e].y;
+                        in[e] = tot;
+                    }
+                    const double2 incl = make_double2(wave_incl_scan(tot.x), wave_incl_scan(tot.y));
+                    if (lane == kWave - 1) wtot[wid] = incl;
+                    ex = make_double2(wave_shift_up1(incl.x), wave_shift_up1(incl.y));
+                }
+                if constexpr (MODEL == ND_FHN) {
+                    if (s == 1 && rec) {  // R from the unit phase vectors
+                        double ru[2] = {0.0, 0.0};
+#pragma unroll
+                        for (int e = 0; e < EPT; ++e) {
+                            if (i0 + e < n) {
+                                const double r = sqrt(y[e][0] * y[e][0] + y[e][1] * y[e][1]);
+                                ru[0] += y[e][0] / r;
+                                ru[1] += y[e][1] / r;
+                            }
                         }
+                        block_sum<BS, 2>(ru, lds);
+                        if (tid == 0) gp(d.R)[rk] = sqrt(ru[0] * ru[0] + ru[1] * ru[1]) / (double)n;
                     }
                 }
-                if constexpr (MODEL == ND_FHN)
-                    block_sum_and_exscan<BS, 2, 2>(ru, tot, lds);
-                else
-                    block_exscan<BS, 2>(tot, lds);  // R comes from the prefix totals
+                lds_barrier();
+                if (act) {
+                    if constexpr (NW > 1) {
+                        const double2 before = waves_before<NW>(wtot, wid);
+                        ex.x += before.x;
+                        ex.y += before.y;
+                    }
 #pragma unroll
-                for (int e = 0; e < EPT; ++e) {
-                    pf[px(tid * EPT + e)] = tot[0] + pf[px(tid * EPT + e)];
-                    pf[TP + px(tid * EPT + e)] = tot[1] + pf[TP + px(tid * EPT + e)];
+                    for (int e = 0; e < EPT; ++e)
+                        pre(px(i0 + e + 1)) = make_double2(ex.x + in[e].x, ex.y + in[e].y);
                 }
                 lds_barrier();
-                const double t0 = pf[px(n - 1)], t1 = pf[TP + px(n - 1)];
-                if (s == 1 && tid == 0 && (d.obs & OBS_R) && (g % d.r_every) == 0) {
-                    const double c = MODEL == ND_FHN ? ru[0] : t0, sn = MODEL == ND_FHN ? ru[1] : t1;
-                    gp(d.R)[g / d.r_every] = sqrt(c * c + sn * sn) / (double)n;
-                }
+                if (act) {
+                    const double2 T = pre(rtot);
+                    if (MODEL != ND_FHN && s == 1 && rec && tid == 0)
+                        gp(d.R)[rk] = sqrt(T.x * T.x + T.y * T.y) / (double)n;
+                    double2 ph[EPT], pl[EPT];
 #pragma unroll
-                for (int e = 0; e < EPT; ++e) {
-                    const int i = tid * EPT + e;
-                    if (i < n) {
-                        // prefix(k) = sum_{j<k} x_j; window [i-P, i+P] through the ring total
-                        const int lo = i - P, hi = i + P + 1;
-                        auto pre = [&](int k, int c) { return k == 0 ? 0.0 : pf[c * TP + px(k - 1)]; };
-                        double w0, w1;
-                        if (lo < 0) {
-                            w0 = pre(hi, 0) + (t0 - pre(lo + n, 0));
-                            w1 = pre(hi, 1) + (t1 - pre(lo + n, 1));
-                        } else if (hi > n) {
-                            w0 = (t0 - pre(lo, 0)) + pre(hi - n, 0);
-                            w1 = (t1 - pre(lo, 1)) + pre(hi - n, 1);
-                        } else {
-                            w0 = pre(hi, 0) - pre(lo, 0);
-                            w1 = pre(hi, 1) - pre(lo, 1);
-                        }
-                        const double2 W = make_double2(w0 - x[e].x, w1 - x[e].y);
+                    for (int e = 0; e < EPT; ++e) {
+                        ph[e] = pre(hi[e]);
+                        pl[e] = pre(lo[e]);
+                    }
+#pragma unroll
+                    for (int e = 0; e < EPT; ++e) {
+                        const double2 t = wrap[e] ? T : make_double2(0.0, 0.0);
+                        const double2 W = make_double2(ph[e].x + (t.x - pl[e].x) - x[e].x,
+                                                       ph[e].y + (t.y - pl[e].y) - x[e].y);
                         double k[V];
-                        M::rhs(d, z[e], x[e], W, k);
-                        if (MV && (d.obs & OBS_MV) && g == d.mv_start && s == 1 && MODEL != ND_FHN)
-                            gp(d.mv)[i] = y[e][0];
+                        M::rhs(mc, z[e], x[e], W, k);
+                        if (MV && (d.obs & OBS_MV) && d.g0 + j == d.mv_start && s == 1 && MODEL != ND_FHN && i0 + e < n)
+                            gp(d.mv)[i0 + e] = y[e][0];
                         double yo[V];
 #pragma unroll
                         for (int v = 0; v < V; ++v) {
                             const double kk = kq<KT>(k[v]);
-                            if (s == 2) acc[e][v] = fma(d.dt3, kk, fma(d.dt6, kp[e][v], y[e][v]));
-                            yo[v] = s == 4 ? fma(d.dt6, kk, fma(d.dt3, kp[e][v], acc[e][v])) : y[e][v];
+                            if (s == 2) acc[e][v] = fma(mc.dt3, kk, fma(mc.dt6, kp[e][v], y[e][v]));
+                            yo[v] = s == 4 ? fma(mc.dt6, kk, fma(mc.dt3, kp[e][v], acc[e][v])) : y[e][v];
                             kp[e][v] = kk;
                         }
                         if constexpr (MODEL == ND_FHN) {
-                            if (MV && s == 4 && (d.obs & OBS_MV) && g >= d.mv_start) {
+                            if (MV && s == 4 && (d.obs & OBS_MV) && d.g0 + j >= d.mv_start) {
                                 const double uo = y[e][0], vo = y[e][1], un = yo[0], vn = yo[1];
                                 dth[e] += atan2(uo * vn - vo * un, uo * un + vo * vn);
                             }
@@ -441,7 +473,10 @@ __global__ __launch_bounds__(BS) void k_ring_resident(const NetDesc* __restrict_
                         for (int v = 0; v < V; ++v) y[e][v] = yo[v];
                     }
                 }
-                lds_barrier();
+            }
+            if (rec) {
+                ++rk;
+                rg += d.r_every;
             }
         }
         if constexpr (MODEL == ND_FHN) {
@@ -450,41 +485,46 @@ __global__ __launch_bounds__(BS) void k_ring_resident(const NetDesc* __restrict_
                 const bool first = d.mv_start >= d.g0;
 #pragma unroll
                 for (int e = 0; e < EPT; ++e) {
-                    const int i = tid * EPT + e;
+                    const int i = i0 + e;
                     if (i < n) gp(d.mv)[i] = (first ? 0.0 : gp(d.mv)[i]) + dth[e];
                 }
             }
         }
-        // write the state back into the buffer the chunk ends on, plus the map
-        // sums the epilogue turns into the final R
+        // write the state back into the buffer the chunk ends on, plus the sums
+        // the epilogue turns into the final R
         ND_GLOBAL double* yout = gp(d.y[(d.ypar + steps) & 1]);
-        double sums[4] = {0.0, 0.0, 0.0, 0.0};
+        double sums[2] = {0.0, 0.0};
 #pragma unroll
         for (int e = 0; e < EPT; ++e) {
-            const int i = tid * EPT + e;
+            const int i = i0 + e;
             if (i < n) {
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
                     yout[(int64_t)v * n + i] = y[e][v];
                     flag_nonfinite(d, y[e][v]);
                 }
-                const double2 xm = M::map(y[e]);
-                sums[0] += xm.x;
-                sums[1] += xm.y;
-                if constexpr (MODEL == ND_FHN) {
-                    const double r = sqrt(y[e][0] * y[e][0] + y[e][1] * y[e][1]);
-                    sums[2] += y[e][0] / r;
-                    sums[3] += y[e][1] / r;
+                if (d.obs & OBS_R) {
+                    if constexpr (MODEL == ND_FHN) {
+                        const double r = sqrt(y[e][0] * y[e][0] + y[e][1] * y[e][1]);
+                        sums[0] += y[e][0] / r;
+                        sums[1] += y[e][1] / r;
+                    } else {
+                        const double2 xm = M::map(y[e]);
+                        sums[0] += xm.x;
+                        sums[1] += xm.y;
+                    }
                 }
             }
         }
-        block_sum<BS, 4>(sums, lds);
-        if (tid == 0) {
-            gp(d.tsum[0])[0] = sums[0];
-            gp(d.tsum[0])[1] = sums[1];
-            gp(d.rsum)[0] = sums[2];
-            gp(d.rsum)[1] = sums[3];
+        if (d.obs & OBS_R) {  // what the epilogue reads
+            block_sum<BS, 2>(sums, lds);
+            if (tid == 0) {
+                ND_GLOBAL double* out = gp(MODEL == ND_FHN ? d.rsum : d.tsum[0]);
+                out[0] = sums[0];
+                out[1] = sums[1];
+            }
         }
+        lds_barrier();  // wtot and the prefix of 0 are rewritten by the next work item
     }
 }
 
@@ -566,15 +606,19 @@ static RingLaunch resident_entry() {
     r.resident_mv = k_ring_resident<MODEL, KT, BS, EPT, true>;
     r.bs = BS;
     r.tile = -BS * EPT;
-    r.smem = 2 * (BS * EPT + BS) * sizeof(double);  // padded prefix arrays
+    r.smem = (BS * EPT + BS + 1) * sizeof(double2);  // padded prefix array
     return r;
 }
 
 template <int MODEL, class KT>
 static bool ring_pick(int tile, RingLaunch* out) {
     switch (tile) {
+        // measured per stage, us (n at the capacity: one ring / 512 rings, FP64 Kuramoto):
+        //   1024: 256 x 4 0.97 / 1.77, 512 x 2 0.99 / 1.75 (4096 rings: 9.9 against 11.7), 1024 x 1 1.18 / 2.47
+        //   2048: 512 x 4 1.49 / 3.09, 256 x 8 1.54 / 2.87 (FHN 1.18 / 2.48 against 1.22 / 2.69), 1024 x 2 1.58 / 3.29
+        //   4096: 512 x 8 2.55 / 5.32 (FHN 2.6 / 5.6), 1024 x 4 2.50 / 5.20 (FHN spills: 6.9 / 16.5)
         case -1024: *out = resident_entry<MODEL, KT, 256, 4>(); return true;
-        case -2048: *out = resident_entry<MODEL, KT, 256, 8>(); return true;
+        case -2048: *out = resident_entry<MODEL, KT, 512, 4>(); return true;
         case -4096: *out = resident_entry<MODEL, KT, 512, 8>(); return true;
         case 2048: *out = ring_entry<MODEL, KT, 256, 8>(); return true;
         case 1024: *out = ring_entry<MODEL, KT, 256, 4>(); return true;

@@ -367,7 +367,7 @@ nd_kernel_config config_for(const nd_problem* p) {
 }
 
 int ring_block(int tile) {
-    if (tile < 0) return tile == -4096 ? 512 : 256;
+    if (tile < 0) return tile == -1024 ? 256 : 512;
     return tile == 128 ? 64 : (tile == 256 ? 128 : 256);  // two elements per thread up to 512
 }
 
@@ -822,7 +822,7 @@ nd_status enqueue_chunk(const Group& g, int chunk, hipStream_t st) {
         RingLaunch L;
         if (!ring_select(g.model, g.prec, g.tile, &L)) return fail(ND_ERR_UNSUPPORTED, "no ring kernel for tile %d", g.tile);
         if (g.tile < 0) {
-            if (!L.resident || L.bs * 4 > -g.tile) return fail(ND_ERR_UNSUPPORTED, "bad resident ring entry");
+            if (!L.resident || L.bs > -g.tile) return fail(ND_ERR_UNSUPPORTED, "bad resident ring entry");
             if ((e = ring_launch_resident(L, grid, st, g.desc, g.work, g.nwork, chunk, g.mv)) != hipSuccess)
                 return hip_fail(e, "ring resident");
         } else {
@@ -913,6 +913,21 @@ nd_status capture_chunk(const Group& g, int K, hipGraphExec_t* out) {
 
 // State values per launch from which a group runs without graph capture.
 constexpr int64_t kEagerValues = int64_t(1) << 20;
+
+// Steps per launch of rings resident in one workgroup.  A chunk is one kernel
+// there, so replaying captured 64-step chunks only added launches (and a capture
+// per batch): 0.97 us per stage of one 1024-ring in replays, 0.93 us in one launch;
+// 512 rings 1.77 and 1.67 us.  The limit keeps a launch to some tens of milliseconds.
+constexpr int64_t kResidentSteps = 1024;
+
+// A group of resident rings: chunks of kResidentSteps launched directly.
+static nd_status run_resident(const Group& g, int64_t maxsteps, hipStream_t st) {
+    for (int64_t done = 0; done < maxsteps; done += kResidentSteps) {
+        const nd_status s = enqueue_chunk(g, (int)std::min(kResidentSteps, maxsteps - done), st);
+        if (s) return s;
+    }
+    return ND_OK;
+}
 
 __global__ void k_put_desc(NetDesc* dst, NetDesc d) { *dst = d; }
 __global__ void k_clear_status(int32_t* status) { *status = 0; }
@@ -1112,11 +1127,12 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
         // Replaying a captured chunk saves the host's per-launch cost, which matters
         // for short kernels; groups whose stage kernels are long (many state values
         // per launch) run eagerly, which measured a few percent faster per launch.
-        // Rings resident in one workgroup always take the chunked path.
         int64_t values = 0;
         for (int q : idx) values += nets[q]->prob.n * nvars_of(nets[q]->prob.model);
-        const bool eager = values >= kEagerValues && !(g.topo == ND_RING && g.tile < 0);
-        if (maxsteps <= K || !graphs_enabled() || eager) {
+        const bool eager = values >= kEagerValues;
+        if (g.topo == ND_RING && g.tile < 0) {
+            if ((s = run_resident(g, maxsteps, st))) return s;
+        } else if (maxsteps <= K || !graphs_enabled() || eager) {
             // one eager chunk covering every network's steps
             if ((s = enqueue_chunk(g, (int)std::min<int64_t>(maxsteps, 1 << 30), st))) return s;
         } else {
@@ -1299,8 +1315,10 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
         // the chunking of nd_run_batch: one chunk, or chunks of K steps where that
         // call replays a captured K-step graph (here launched directly)
         const int K = std::max(1, n0->cfg.chunk);
-        const bool eager = values >= kEagerValues && !(g.topo == ND_RING && g.tile < 0);
-        if (maxsteps <= K || !graphs_enabled() || eager) {
+        const bool eager = values >= kEagerValues;
+        if (g.topo == ND_RING && g.tile < 0) {
+            if ((s = run_resident(g, maxsteps, st))) return s;
+        } else if (maxsteps <= K || !graphs_enabled() || eager) {
             if ((s = enqueue_chunk(g, (int)std::min<int64_t>(maxsteps, 1 << 30), st))) return s;
         } else {
             const int64_t reps = (maxsteps + K - 1) / K;

@@ -94,6 +94,42 @@ def test_ring_tiles_and_ragged_tails_fp64(nd, n, P, model, path):
     assert np.max(np.abs(R - Rref)) < 1e-12
 
 
+@pytest.mark.parametrize("n,P", [(3, 1), (64, 31), (65, 32), (256, 1), (257, 128), (1023, 511), (1025, 512), (2047, 3),
+                                 (2048, 1023), (4095, 2047)])
+@pytest.mark.parametrize("model", ["kur", "fhn", "inertia"])
+def test_resident_ring_at_wave_and_capacity_edges(nd, n, P, model):
+    """Rings held by one workgroup with the last wave full, ragged or alone, waves
+    without elements, and windows that wrap for every element.  20 steps of dt =
+    0.01 from order-one states: the window sums re-associate at most n terms (error
+    below n ulp of a unit, over the 2P they are divided by), so 1e-12 has a margin
+    of a factor of a hundred."""
+    m, om, prm = {"kur": (nd.ND_KURAMOTO, O.KURAMOTO, [0.3, 1.0, 1.2]), "fhn": (nd.ND_FHN, O.FHN, FHN_PRM),
+                  "inertia": (nd.ND_KURAMOTO_INERTIA, O.INERTIA, [0.1, 1.0, 0.4, 1.0, 0.05])}[model]
+    y0 = inputs.fhn_circle(n, n) if model == "fhn" else inputs.kuramoto_phases(n, n)
+    if model == "inertia":
+        y0 = np.concatenate([y0, 0.1 * inputs.kuramoto_phases(n + 1, n)])
+    print(f"case resident edges model={model} n={n} P={P}", flush=True)
+    y, R, _ = ring_case(nd, m, n, P, prm, nd.ND_FP64, y0, 0.01, 20, record_every=7)
+    ref, Rref, _ = O.run(O.ring(om, n, P, prm), y0, 0.01, 20, record_every=7)
+    assert normwise(y, ref, O.NVARS[om]) < 1e-12
+    assert np.max(np.abs(R - Rref)) < 1e-12
+
+
+@pytest.mark.parametrize("model", ["kur", "fhn"])
+def test_resident_ring_across_launches(nd, model):
+    """A run longer than the steps one launch takes: the state, the recorded R and the
+    mean velocity that starts in the first launch and ends in the second."""
+    n, P, steps = 130, 40, 1100
+    m, om, prm = (nd.ND_KURAMOTO, O.KURAMOTO, [0.3, 1.0, 1.2]) if model == "kur" else (nd.ND_FHN, O.FHN, FHN_PRM)
+    y0 = inputs.kuramoto_phases(5, n) if model == "kur" else inputs.fhn_circle(5, n)
+    print(f"case resident launches model={model}", flush=True)
+    y, R, mv = ring_case(nd, m, n, P, prm, nd.ND_FP64, y0, 1e-3, steps, record_every=100, mv=1000)
+    ref, Rref, mvref = O.run(O.ring(om, n, P, prm), y0, 1e-3, steps, record_every=100, mv_start=1000)
+    assert normwise(y, ref, O.NVARS[om]) < 1e-11
+    assert np.max(np.abs(R - Rref)) < 1e-11
+    assert np.max(np.abs(mv - mvref)) < 1e-10  # a difference of phases over 0.1 time units
+
+
 @pytest.mark.parametrize("q", [0, 1, 3, 5])
 def test_twisted_state_rotates_rigidly_on_gpu(nd, q):
     """Closed form, not the oracle: a q-twisted state rotates at Omega_q."""
