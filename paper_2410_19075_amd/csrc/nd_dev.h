@@ -11,6 +11,24 @@ namespace nd {
 
 constexpr int kWave = 64;
 constexpr int kCsrSourceBlocks = 8;  // CSR in-edges split by source range, one block per XCD
+// CSR: target rows per work item.  More rows put more edges on a cache line of a
+// chunk's sources; below 2^16 rows 512 would leave CUs idle (8 work items per row
+// tile): us per stage with 256 / 512, 2000 neurons of degree 50 7.9 / 10.2, 20000
+// neurons 9.7 / 12.0.
+__host__ __device__ constexpr int csr_rows(int64_t n) { return n < (int64_t(1) << 16) ? 256 : 512; }
+constexpr int kCsrSlotBits = 13;    // CSR: bits of an edge's place inside its chunk
+constexpr int kCsrChunk = 1 << kCsrSlotBits;  // CSR: edges whose products are in LDS at once
+// Edges are stored as (source - block begin) << kCsrSlotBits | slot where that
+// fits 32 bits, sorted by source inside each chunk; in larger networks (where a
+// chunk holds less than one edge per eight cache lines of its block, so that
+// sorting gains nothing) as the source alone, in row order.
+__host__ __device__ constexpr bool csr_packed(int64_t n) {
+    return (n + kCsrSourceBlocks - 1) / kCsrSourceBlocks <= (int64_t(1) << (32 - kCsrSlotBits));
+}
+// First source of block b: the smallest src with src * blocks / n >= b.
+__host__ __device__ constexpr int64_t csr_block_begin(int b, int64_t n) {
+    return (b * n + kCsrSourceBlocks - 1) / kCsrSourceBlocks;
+}
 constexpr int kLinksRows = 256;          // compressed coupling matrix: rows per work item
 constexpr int32_t kLinksRemove = 1 << 30;  // entry position flag: the entry removes a link of V
 
@@ -36,7 +54,7 @@ struct NetDesc {
     double* rsum;       // FHN: per-tile sums of the unit phase vectors (u, v)/|(u, v)|
     void* sx[2];        // HH: exchanged synaptic activations S(V) per stage
     const int64_t* row_ptr;  // CSR: per source block b, row offsets at [b*(n+1), (b+1)*(n+1))
-    const int32_t* col;      // CSR: sources, block-major, ascending within each row and block
+    const uint32_t* col;     // CSR: edges, block-major (see csr_packed)
     const void* w;           // CSR: weights in the bulk type, same order
     double* acc_part;        // CSR: per source block synaptic partial sums [blocks][n]
     const double* iapp;

@@ -38,6 +38,7 @@ struct Net {
     nd_problem prob{};        // copy without host pointers
     nd_kernel_config cfg{};
     NetDesc tmpl{};           // device pointers and derived constants
+    int csr_edges = 0;        // CSR: edges of the largest chunk
     int ypar = 0;             // y buffer holding the current state
     int64_t last_steps = 0;
     int64_t r_every = 0;
@@ -79,6 +80,9 @@ struct Net {
     nd_status create(const nd_problem* p);
     nd_status apply_config(const nd_kernel_config& c);
     int64_t work_items() const;
+    // what the kernel shape of a class depends on besides model, precision and tile:
+    // lattices the (half-)width, CSR the rows per work item
+    int shape_key() const;
     void append_work(int desc_index, std::vector<int2>& wk) const;
     nd_status prepare_observe(int64_t steps, const nd_observe* obs, bool may_alloc = true);
     NetDesc run_desc(double dt, int64_t steps) const;
@@ -93,8 +97,9 @@ struct Net {
 // Networks of one kernel class launched together.
 struct Group {
     int model, topo, prec, tile;
-    int tile_y, h;  // cube: y tile extent and half-width (kernel shape)
+    int tile_y, h;  // cube: y tile extent; Net::shape_key
     int block;      // ball: workgroup size (256 or 1024)
+    int edges = kCsrChunk;  // CSR: edges of the largest chunk of its networks
     bool mv;        // some network records the mean phase velocity
     int ndesc;
     int grid;
@@ -175,16 +180,18 @@ hipError_t cube_launch_stage(const CubeLaunch& L, int grid, int block, size_t sm
 hipError_t cube_launch_final(const CubeLaunch& L, int grid, hipStream_t s, NetDesc* D, const int2* work,
                              const int* nwork, int chunk);
 
-// CSR kernels (csr.hip): work items of 256 target rows
+// CSR kernels (csr.hip): work items of csr_rows target rows; `edges` bounds the
+// edges of every chunk (its products' LDS)
 struct CsrLaunch {
     void (*gather)(const NetDesc*, const int2*, const int*, int, int);
     void (*update[4])(const NetDesc*, const int2*, const int*, int);
     void (*prologue)(const NetDesc*, const int2*, const int*);
+    int rows;  // target rows per work item = threads per workgroup
 };
-bool csr_select(int prec, int ept, CsrLaunch* out);
+bool csr_select(int prec, int ept, int rows, CsrLaunch* out);
 hipError_t csr_launch_prologue(const CsrLaunch& L, int grid, hipStream_t s, NetDesc* D, const int2* work,
                                const int* nwork);
-hipError_t csr_launch_stage(const CsrLaunch& L, int grid, hipStream_t s, NetDesc* D, const int2* work,
+hipError_t csr_launch_stage(const CsrLaunch& L, int grid, int edges, hipStream_t s, NetDesc* D, const int2* work,
                             const int* nwork, int stage, int j);
 
 // Binary coupling matrices in the paper's compressed form (links.hip)

@@ -352,8 +352,12 @@ nd_kernel_config default_config(const nd_problem* p) {
         c.tile = kLinksRows;  // rows per work item
         c.block = 256;
     } else {
-        c.tile = 256;    // target rows per work item
-        c.tile_y = 8;    // edges per thread per chunk
+        c.tile = 256;
+        // edges per thread in flight: as many as the mean (512-row tile, source block)
+        // half fills.  2e5 neurons, us per stage with 4 / 8 / 16 (FP64): degree 100
+        // 88 / 81 / 73, degree 10 27 / 29 / 34 (more registers, fewer waves)
+        const int64_t edges = p->nnz / kCsrSourceBlocks * 512 / p->n;
+        c.tile_y = edges > 8 * 512 ? 16 : edges > 4 * 512 ? 8 : 4;
         c.block = 256;
     }
     return c;
@@ -556,6 +560,49 @@ static void derive_params(const nd_problem* p, NetDesc& d) {
     }
 }
 
+// Sort the edges of every chunk (the kCsrChunk-edge pieces of a row tile's edges
+// of one source block) by source and pack each with its place in row order; the
+// weights follow.  Two counting passes over the source's bits per chunk.
+static void csr_sort_chunks(int64_t n, const std::vector<int64_t>& bptr, std::vector<uint32_t>& col,
+                            std::vector<double>& w) {
+    constexpr int kBits = 10, kBuckets = 1 << kBits;
+    const int64_t rows = csr_rows(n);
+    static_assert(32 - kCsrSlotBits <= 2 * kBits, "two passes cover the source bits");
+    std::vector<uint32_t> a(kCsrChunk), t(kCsrChunk);
+    std::vector<double> wr(kCsrChunk);
+    std::vector<int> cnt[2] = {std::vector<int>(kBuckets), std::vector<int>(kBuckets)};
+    for (int b = 0; b < kCsrSourceBlocks; ++b) {
+        const int64_t* p = bptr.data() + (size_t)b * (n + 1);
+        const uint32_t base = (uint32_t)csr_block_begin(b, n);
+        for (int64_t r0 = 0; r0 < n; r0 += rows) {
+            const int64_t e1 = p[std::min(r0 + rows, n)];
+            for (int64_t c0 = p[r0]; c0 < e1; c0 += kCsrChunk) {
+                const int m = (int)std::min<int64_t>(kCsrChunk, e1 - c0);
+                for (auto& c : cnt) std::fill(c.begin(), c.end(), 0);
+                for (int q = 0; q < m; ++q) {
+                    const uint32_t v = col[c0 + q] - base;
+                    a[q] = v << kCsrSlotBits | (uint32_t)q;
+                    ++cnt[0][v & (kBuckets - 1)];
+                    ++cnt[1][v >> kBits];
+                }
+                for (auto& c : cnt)
+                    for (int o = 0, i = 0; i < kBuckets; ++i) {
+                        const int k = c[i];
+                        c[i] = o;
+                        o += k;
+                    }
+                for (int q = 0; q < m; ++q) t[cnt[0][a[q] >> kCsrSlotBits & (kBuckets - 1)]++] = a[q];
+                for (int q = 0; q < m; ++q) a[cnt[1][t[q] >> (kCsrSlotBits + kBits)]++] = t[q];
+                std::copy(w.begin() + c0, w.begin() + c0 + m, wr.begin());
+                for (int q = 0; q < m; ++q) {
+                    col[c0 + q] = a[q];
+                    w[c0 + q] = wr[a[q] & (kCsrChunk - 1)];
+                }
+            }
+        }
+    }
+}
+
 nd_status Net::create(const nd_problem* pr) {
     HIPC(hipGetDevice(&dev));
     prob = *pr;
@@ -584,12 +631,23 @@ nd_status Net::create(const nd_problem* pr) {
     if (pr->topo == ND_CSR) {
         // split every row's in-edges by source block (sources ascending, so each
         // block keeps its order) and lay the blocks out one after the other
-        const int B = kCsrSourceBlocks;
+        constexpr int B = kCsrSourceBlocks;
         const int64_t nnz = pr->nnz;
         std::vector<int64_t> bptr((size_t)B * (n + 1), 0);
-        auto block_of = [&](int64_t src) { return (int)std::min<int64_t>(B - 1, src * B / n); };
+        int64_t begin[B + 1];  // first source of each block
+        for (int b = 0; b <= B; ++b) begin[b] = csr_block_begin(b, n);
+        // block of a source, starting from the block of the row's last one (sources
+        // usually ascend: no division per edge)
+        auto block_of = [&](int64_t src, int b) {
+            while (src < begin[b]) --b;
+            while (src >= begin[b + 1]) ++b;
+            return b;
+        };
         for (int64_t i = 0; i < n; ++i)
-            for (int64_t e = pr->row_ptr[i]; e < pr->row_ptr[i + 1]; ++e) ++bptr[(size_t)block_of(pr->col[e]) * (n + 1) + i + 1];
+            for (int64_t e = pr->row_ptr[i], b = 0; e < pr->row_ptr[i + 1]; ++e) {
+                b = block_of(pr->col[e], (int)b);
+                ++bptr[(size_t)b * (n + 1) + i + 1];
+            }
         int64_t base = 0;
         for (int b = 0; b < B; ++b) {
             int64_t* p = bptr.data() + (size_t)b * (n + 1);
@@ -598,14 +656,22 @@ nd_status Net::create(const nd_problem* pr) {
             base = p[n];
         }
         std::vector<int64_t> pos(bptr);
-        std::vector<int32_t> col2((size_t)std::max<int64_t>(nnz, 1));
+        std::vector<uint32_t> col2((size_t)std::max<int64_t>(nnz, 1));
         std::vector<double> w2((size_t)std::max<int64_t>(nnz, 1));
         for (int64_t i = 0; i < n; ++i)
-            for (int64_t e = pr->row_ptr[i]; e < pr->row_ptr[i + 1]; ++e) {
-                const int b = block_of(pr->col[e]);
+            for (int64_t e = pr->row_ptr[i], b = 0; e < pr->row_ptr[i + 1]; ++e) {
+                b = block_of(pr->col[e], (int)b);
                 const int64_t dst = pos[(size_t)b * (n + 1) + i]++;
-                col2[dst] = pr->col[e];
+                col2[dst] = (uint32_t)pr->col[e];
                 w2[dst] = pr->weight[e];
+            }
+        if (csr_packed(n)) csr_sort_chunks(n, bptr, col2, w2);
+        csr_edges = 1;
+        for (int b = 0; b < B; ++b)
+            for (int64_t r0 = 0; r0 < n; r0 += csr_rows(n)) {
+                const int64_t* p = bptr.data() + (size_t)b * (n + 1);
+                const int64_t m = p[std::min<int64_t>(r0 + csr_rows(n), n)] - p[r0];
+                csr_edges = (int)std::min<int64_t>(kCsrChunk, std::max<int64_t>(csr_edges, m));
             }
         if ((s = alloc((void**)&d.row_ptr, (size_t)B * (n + 1) * 8))) return s;
         if ((s = alloc((void**)&d.col, std::max<int64_t>(nnz, 1) * 4))) return s;
@@ -699,9 +765,9 @@ nd_status Net::apply_config(const nd_kernel_config& c) {
         tmpl.G = (int32_t)((n + kLinksRows - 1) / kLinksRows);
     } else {
         cfg.block = 256;
-        cfg.tile = 256;  // rows per work item (fixed by the kernel)
-        tmpl.tile = 256;
-        tmpl.G = (int32_t)(kCsrSourceBlocks * ((n + 255) / 256));  // (row tile, source block)
+        cfg.tile = 256;  // the one accepted value (the kernels take csr_rows(n) rows per work item)
+        tmpl.tile = csr_rows(n);
+        tmpl.G = (int32_t)(kCsrSourceBlocks * ((n + csr_rows(n) - 1) / csr_rows(n)));  // (row tile, source block)
     }
     nd_status s;
     if (prob.topo != ND_CSR) {
@@ -719,6 +785,11 @@ nd_status Net::apply_config(const nd_kernel_config& c) {
 }
 
 int64_t Net::work_items() const { return tmpl.G; }
+
+int Net::shape_key() const {
+    if (prob.topo == ND_CSR) return csr_rows(prob.n);
+    return prob.topo == ND_CUBE3D || prob.topo == ND_BALL3D || prob.topo == ND_DISK2D ? (int)prob.radius : 0;
+}
 
 void Net::append_work(int desc_index, std::vector<int2>& wk) const {
     const int64_t m = work_items();
@@ -867,11 +938,11 @@ nd_status enqueue_chunk(const Group& g, int chunk, hipStream_t st) {
             return hip_fail(e, "links chunk");
     } else {
         CsrLaunch L;
-        if (!csr_select(g.prec, g.tile_y, &L)) return fail(ND_ERR_UNSUPPORTED, "no CSR kernel for %d edges per thread", g.tile_y);
+        if (!csr_select(g.prec, g.tile_y, g.h, &L)) return fail(ND_ERR_UNSUPPORTED, "no CSR kernel for %d edges per thread", g.tile_y);
         if ((e = csr_launch_prologue(L, grid, st, g.desc, g.work, g.nwork)) != hipSuccess) return hip_fail(e, "csr prologue");
         for (int j = 0; j < chunk; ++j)
             for (int s = 1; s <= 4; ++s)
-                if ((e = csr_launch_stage(L, grid, st, g.desc, g.work, g.nwork, s, j)) != hipSuccess)
+                if ((e = csr_launch_stage(L, grid, g.edges, st, g.desc, g.work, g.nwork, s, j)) != hipSuccess)
                     return hip_fail(e, "csr stage");
     }
     hipLaunchKernelGGL(k_advance, dim3((g.ndesc + 255) / 256), dim3(256), 0, st, g.desc, g.ndesc, chunk);
@@ -1063,10 +1134,9 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
     for (int i = 0; i < count; ++i) {
         if (steps[i] == 0) continue;
         const Net* n = nets[i];
-        const int h = n->prob.topo == ND_CUBE3D || n->prob.topo == ND_BALL3D || n->prob.topo == ND_DISK2D
-                          ? (int)n->prob.radius : 0;
         const int bs = (n->prob.topo == ND_BALL3D || n->prob.topo == ND_DISK2D) ? n->cfg.block : 0;
-        groups[std::make_tuple(n->prob.model, n->prob.topo, n->prob.precision, n->cfg.tile, n->cfg.tile_y, h, bs)]
+        groups[std::make_tuple(n->prob.model, n->prob.topo, n->prob.precision, n->cfg.tile, n->cfg.tile_y,
+                               n->shape_key(), bs)]
             .push_back(i);
     }
     for (auto& kv : groups) {
@@ -1082,8 +1152,10 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
         g.ndesc = (int)idx.size();
         int64_t maxsteps = 0, nwork = 0;
         g.mv = false;
+        g.edges = 0;
         for (int q : idx) {
             g.mv = g.mv || nets[q]->mv_start >= 0;
+            g.edges = std::max(g.edges, nets[q]->csr_edges);
             nwork += nets[q]->work_items();
             maxsteps = std::max(maxsteps, steps[q]);
         }
@@ -1266,10 +1338,9 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
         grp[i] = -1;
         if (steps[i] == 0) continue;
         const Net* n = nets[i];
-        const bool lattice = n->prob.topo == ND_CUBE3D || n->prob.topo == ND_BALL3D || n->prob.topo == ND_DISK2D;
         const bool ball = n->prob.topo == ND_BALL3D || n->prob.topo == ND_DISK2D;
         const int k[7] = {n->prob.model, n->prob.topo, n->prob.precision, n->cfg.tile, n->cfg.tile_y,
-                          lattice ? (int)n->prob.radius : 0, ball ? n->cfg.block : 0};
+                          n->shape_key(), ball ? n->cfg.block : 0};
         int gi = 0;
         while (gi < ngroups && std::memcmp(key[gi], k, sizeof k) != 0) ++gi;
         if (gi == ngroups) std::memcpy(key[ngroups++], k, sizeof k);
@@ -1291,6 +1362,7 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
         g.work = works + wnext;
         g.nwork = counts + gi;
         g.mv = false;
+        g.edges = 0;
         int64_t maxsteps = 0, nwork = 0, values = 0;
         int first = -1;
         for (int i = 0; i < count; ++i) {
@@ -1301,6 +1373,7 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
                 return hip_fail(e, "descriptor upload");
             ++g.ndesc;
             g.mv = g.mv || n->mv_start >= 0;
+            g.edges = std::max(g.edges, n->csr_edges);
             nwork += n->work_items();
             values += n->prob.n * nvars_of(n->prob.model);
             maxsteps = std::max(maxsteps, steps[i]);

@@ -187,3 +187,79 @@ def test_hh_full_size_fp32_bulk_200_steps_against_fp64(nd, hh_full):
     e = normwise(hh_run(nd, hh_full, 1, 200), hh_run(nd, hh_full, 0, 200))
     print(f"hh 1e6 fp32-bulk vs fp64 after 200 steps {e:.3e}")
     assert e < 1e-4
+
+
+def run_net(nd, n, graph, steps, prec=0, seed=3):
+    rp, col, w = graph
+    iapp, y0 = inputs.hh_iapp(seed, n), inputs.hh_state(seed, n)
+    p = nd.problem(nd.ND_HH, nd.ND_CSR, n, HH_PRM, precision=prec, row_ptr=rp, col=col, weight=w, per_elem=iapp)
+    y, _, _ = nd.simulate(p, y0, 0.01, steps)
+    return y, p, y0, iapp
+
+
+def test_hh_hub_row_spans_sorted_chunks(nd):
+    """A row with more in-edges of one source block (10^4) than a chunk holds: its
+    products are added over two chunks of sorted edges.  1e-12 as for every FP64
+    run of a few steps: each row's products are added in edge order."""
+    n = 80000
+    g = hub_graph(n, 2, 7, np.arange(600, 700), 12)
+    print("case hh hub over sorted chunks", flush=True)
+    y, _, y0, iapp = run_net(nd, n, g, 3)
+    ref, _, _ = O.run(O.csr(n, *g, HH_PRM, iapp), y0, 0.01, 3)
+    assert normwise(y, ref) < 1e-12
+
+
+def test_hh_rows_in_any_order(nd):
+    """Rows whose sources are not ascending: the sums take the given order inside a
+    source block, so two orders of the same rows agree to rounding (1e-13)."""
+    n, deg = 5000, 40
+    rp, col, w = inputs.random_out_graph(4, n, deg)
+    rng = np.random.default_rng(4)
+    order = np.lexsort((rng.random(col.size), np.repeat(np.arange(n), np.diff(rp))))
+    print("case hh rows in any order", flush=True)
+    a = run_net(nd, n, (rp, col, w), 5)[0]
+    b = run_net(nd, n, (rp, col[order].copy(), w[order].copy()), 5)[0]
+    assert normwise(b, a) < 1e-13
+
+
+@pytest.mark.parametrize("extra", [0, 1])
+def test_hh_largest_packed_and_first_unpacked_size(nd, extra):
+    """2^22 neurons, the most whose edges pack a source and a slot into one word,
+    and one more, which keeps plain sources: in-edges from both ends of every
+    source block, one step against the oracle."""
+    n = (1 << 22) + extra
+    i = np.arange(n, dtype=np.int64)
+    block = (i * 2654435761) % 8
+    first = (block * n + 7) // 8
+    last = ((block + 1) * n + 7) // 8 - 1
+    col = np.stack([first, last], 1).astype(np.int32).ravel()
+    rp = 2 * np.arange(n + 1, dtype=np.int64)
+    w = inputs.uniform(6, inputs.TAG_WEIGHT, 2 * n) * 0.1
+    print(f"case hh n={n}", flush=True)
+    y, _, y0, iapp = run_net(nd, n, (rp, col, w), 1)
+    ref, _, _ = O.run(O.csr(n, rp, col, w, HH_PRM, iapp), y0, 0.01, 1)
+    assert normwise(y, ref) < 1e-12
+
+
+def test_hh_batch_of_mixed_sizes_and_degrees(nd):
+    """Networks with 256 and 512 rows per work item and every default of edges per
+    thread in one batch call: the same bits as alone."""
+    cases = [(700, 5), (3000, 100), (70000, 3), (66000, 40), (1500, 90)]
+    print("case hh mixed batch", flush=True)
+    alone, hs, y0s = [], [], []
+    try:
+        for n, deg in cases:
+            y, p, y0, _ = run_net(nd, n, inputs.random_out_graph(deg, n, deg), 4)
+            alone.append(y)
+            y0s.append(y0)
+            hs.append(nd.nd_create(p))
+        for h, y0 in zip(hs, y0s):
+            nd.nd_set_state(h, y0, on_device=0)
+        nd.nd_run_batch(hs, [0.01] * len(hs), [4] * len(hs))
+        for h, y in zip(hs, alone):
+            got = np.empty_like(y)
+            nd.nd_get_state(h, got, on_device=0)
+            assert np.array_equal(got, y)
+    finally:
+        for h in hs:
+            nd.nd_destroy(h)
