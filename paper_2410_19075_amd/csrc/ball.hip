@@ -103,13 +103,13 @@ void k_ball_scatter(const NetDesc* __restrict__ D, const int2* __restrict__ work
     constexpr int S = 2 * P + 1;
     extern __shared__ double2 smem[];  // [2][HY][RW] row prefix planes
     __shared__ double lds[2 * kScatterWaves];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     const int nvb = ((nwork + 7) >> 3) << 3;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     for (int vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
         const int w = xcd_work(vb, nwork);
         if (w < 0) continue;
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (j >= d.nsteps) continue;  // uniform over the block
         const int n1 = d.n1, n2 = d.n2, n3 = d.n3;

@@ -63,12 +63,12 @@ __device__ __forceinline__ T synapse(const double* p, double V) {
 template <class KT, int ROWS>
 __global__ __launch_bounds__(ROWS) void k_csr_prologue(const NetDesc* __restrict__ D, const int2* __restrict__ work,
                                                      const int* __restrict__ nwork_p) {
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     // one row tile per workgroup: the tile's work items are 8 consecutive
     // entries starting at a multiple of 8; spreading the tiles over the
     // workgroups (rather than taking every 8th workgroup) keeps all XCDs busy
     for (int v = blockIdx.x; v < nwork / kSrcBlocks; v += gridDim.x) {
-        const int2 wk = work[v * kSrcBlocks];
+        const int2 wk = work_at(work, v * kSrcBlocks);
         const NetDesc& d = D[wk.x];
         if (d.g0 != 0 || d.nsteps <= 0) continue;
         const int64_t i = (int64_t)(wk.y / kSrcBlocks) * ROWS + threadIdx.x;
@@ -99,10 +99,10 @@ __global__ __launch_bounds__(ROWS) __attribute__((amdgpu_waves_per_eu(4))) void 
     constexpr int BS = ROWS;
     extern __shared__ double prod[];  // the largest chunk of the group's networks
     __shared__ int64_t rb[ROWS + 1];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     const int tid = threadIdx.x;
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (j >= d.nsteps) continue;  // uniform over the block
         const int64_t n = d.n;
@@ -171,10 +171,10 @@ template <class KT, int STAGE, int ROWS>
 __global__ __launch_bounds__(ROWS) void k_csr_update(const NetDesc* __restrict__ D, const int2* __restrict__ work,
                                                    const int* __restrict__ nwork_p, int j) {
     constexpr int stage = STAGE;
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     const int tid = threadIdx.x;
     for (int v = blockIdx.x; v < nwork / kSrcBlocks; v += gridDim.x) {  // one row tile per workgroup
-        const int2 wk = work[v * kSrcBlocks];
+        const int2 wk = work_at(work, v * kSrcBlocks);
         const NetDesc& d = D[wk.x];
         if (j >= d.nsteps) continue;
         const int64_t n = d.n;

@@ -66,13 +66,13 @@ __global__ __launch_bounds__(1024) void k_cube_stage(const NetDesc* __restrict__
     constexpr int stage = STAGE;
     extern __shared__ double2 smem[];
     __shared__ double lds[2 * 16];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     const int nvb = ((nwork + 7) >> 3) << 3;
     const int tid = threadIdx.x;
     for (int vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
         const int w = xcd_work(vb, nwork);
         if (w < 0) continue;
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (j >= d.nsteps) continue;  // uniform over the block
         const int n1 = d.n1, n2 = d.n2, n3 = d.n3;
@@ -486,13 +486,13 @@ __global__ __launch_bounds__(BS) void k_ball_stage(const NetDesc* __restrict__ D
     // ({0, 0, 0, 0}: hi - lo = 0 exactly) to a multiple of kBallUnroll
     __shared__ int4 runs[kBallMaxRuns];
     __shared__ int nruns;
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     const int nvb = ((nwork + 7) >> 3) << 3;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
     for (int vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
         const int w = xcd_work(vb, nwork);
         if (w < 0) continue;
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (j >= d.nsteps) continue;  // uniform over the block
         const int n1 = d.n1, n2 = d.n2, n3 = d.n3, P = (int)d.P;
@@ -686,11 +686,13 @@ __global__ __launch_bounds__(256) void k_cube_final_partials(const NetDesc* __re
                                                              const int* __restrict__ nwork_p, int chunk) {
     using M = RingModel<ND_KURAMOTO, KT>;
     __shared__ double lds[2 * 16];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (d.nsteps <= 0 || d.nsteps > chunk) continue;
+        const bool rec = (d.obs & OBS_R) && (d.g0 + d.nsteps) % d.r_every == 0;
+        if (!rec && !(d.obs & OBS_MV)) continue;  // nothing recorded at the end: no pass over the state
         const int64_t n = d.n;
         const int64_t per = (n + d.G - 1) / d.G;
         const int64_t b = (int64_t)wk.y * per, e = min(n, b + per);
@@ -714,9 +716,9 @@ __global__ __launch_bounds__(256) void k_cube_final_partials(const NetDesc* __re
 __global__ __launch_bounds__(256) void k_cube_final_R(const NetDesc* __restrict__ D, const int2* __restrict__ work,
                                                       const int* __restrict__ nwork_p, int chunk) {
     __shared__ double lds[2 * 16];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (wk.y != 0 || d.nsteps <= 0 || d.nsteps > chunk || !(d.obs & OBS_R)) continue;
         const int64_t gend = d.g0 + d.nsteps;

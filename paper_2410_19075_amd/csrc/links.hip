@@ -199,9 +199,9 @@ __global__ __launch_bounds__(256) void k_links_prologue(const NetDesc* __restric
     using MT2 = typename LinksTypes<MODEL, KT>::MT2;
     constexpr int V = M::V;
     __shared__ double lds[2 * 4];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (d.g0 != 0 || d.nsteps <= 0) continue;
         const int64_t n = d.n;
@@ -239,14 +239,14 @@ __global__ __launch_bounds__(256) void k_links_stage(const NetDesc* __restrict__
     using MT2 = typename LinksTypes<MODEL, KT>::MT2;
     constexpr int V = M::V, stage = STAGE;
     __shared__ double lds[2 * 4];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     const int tid = threadIdx.x;
     // neighbouring row tiles share most of their gathers: keep them on one XCD
     const int nvb = ((nwork + 7) >> 3) << 3;
     for (int vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
         const int w = xcd_work(vb, nwork);
         if (w < 0) continue;
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (j >= d.nsteps) continue;  // uniform over the block
         const int64_t n = d.n, g = d.g0 + j;
@@ -388,9 +388,9 @@ template <int MODEL>
 __global__ __launch_bounds__(256) void k_links_final(const NetDesc* __restrict__ D, const int2* __restrict__ work,
                                                     const int* __restrict__ nwork_p, int chunk) {
     __shared__ double lds[2 * 4];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (d.nsteps <= 0 || d.nsteps > chunk) continue;
         const int64_t n = d.n, gend = d.g0 + d.nsteps;

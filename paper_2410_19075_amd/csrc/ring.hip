@@ -32,9 +32,9 @@ __global__ __launch_bounds__(BS) void k_ring_prologue(const NetDesc* __restrict_
     using M = RingModel<MODEL, KT>;
     constexpr int V = M::V, T = BS * EPT, NW = BS / kWave;
     __shared__ double lds[4 * NW];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (d.g0 != 0 || d.nsteps <= 0) continue;
         const int64_t n = d.n, t0 = (int64_t)wk.y * T;
@@ -83,14 +83,14 @@ __global__ __launch_bounds__(BS) void k_ring_stage(const NetDesc* __restrict__ D
     constexpr bool kNeedY = STAGE != 4 || MV, kNeedK = STAGE == 2 || STAGE == 4;
     __shared__ double sy[kNeedY ? V * T : 1], sk[kNeedK ? V * T : 1];
     __shared__ double lds[8 * NW];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     const int tid = threadIdx.x;
     // virtual block ids keep blockIdx.x % 8 (grid is a multiple of 8 or == nwork)
     const int nvb = ((nwork + 7) >> 3) << 3;
     for (int vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
         const int w = xcd_work(vb, nwork);
         if (w < 0) continue;
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (j >= d.nsteps) continue;  // uniform over the block
         // element indices and the per-variable offsets below are 32-bit (rings
@@ -345,11 +345,11 @@ __global__ __launch_bounds__(BS) void k_ring_resident(const NetDesc* __restrict_
     auto pre = [&](int off) -> double2& { return *(double2*)(pf + off); };
     __shared__ double2 wtot[NW];
     __shared__ double lds[4 * NW];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     const int tid = threadIdx.x, lane = tid & (kWave - 1), i0 = tid * EPT;
     const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (d.nsteps <= 0) continue;
         const ModelConst mc(d);  // read once: through d they were scalar loads in every stage
@@ -536,9 +536,9 @@ __global__ __launch_bounds__(BS) void k_ring_epilogue(const NetDesc* __restrict_
                                                       const int* __restrict__ nwork_p, int chunk) {
     constexpr int T = BS * EPT, NW = BS / kWave;
     __shared__ double lds[2 * NW];
-    const int nwork = *nwork_p;
+    const int nwork = work_count(D, nwork_p);
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
-        const int2 wk = work[w];
+        const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (d.nsteps <= 0 || d.nsteps > chunk) continue;
         const int64_t n = d.n, gend = d.g0 + d.nsteps;

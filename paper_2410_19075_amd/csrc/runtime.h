@@ -46,9 +46,7 @@ struct Net {
     double* R_dev = nullptr;
     int64_t R_cap = 0;
     double* mv_dev = nullptr;
-    NetDesc* solo_desc = nullptr;  // launch arrays for running this network alone
-    int2* solo_work = nullptr;
-    int* solo_count = nullptr;
+    NetDesc* solo_desc = nullptr;  // descriptor for running this network alone
     int32_t* status_dev = nullptr;   // status word the stage kernels flag (non-finite state)
     int32_t* status_host = nullptr;  // pinned copy, read after a synchronising call
     hipEvent_t last_ev = nullptr;    // recorded after the last work enqueued for this network alone
@@ -83,7 +81,6 @@ struct Net {
     // what the kernel shape of a class depends on besides model, precision and tile:
     // lattices the (half-)width, CSR the rows per work item
     int shape_key() const;
-    void append_work(int desc_index, std::vector<int2>& wk) const;
     nd_status prepare_observe(int64_t steps, const nd_observe* obs, bool may_alloc = true);
     NetDesc run_desc(double dt, int64_t steps) const;
     // chunked runs (serving): the run's step counter lives on the host and each

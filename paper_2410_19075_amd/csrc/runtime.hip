@@ -716,7 +716,6 @@ nd_status Net::create(const nd_problem* pr) {
         HIPC(setup_copy(astream, (void*)d.linv, f.inv.data(), K * 8));
     }
     if ((s = alloc((void**)&solo_desc, sizeof(NetDesc)))) return s;
-    if ((s = alloc((void**)&solo_count, 2 * sizeof(int)))) return s;
     if ((s = alloc((void**)&status_dev, sizeof(int32_t)))) return s;
     HIPC(astream ? hipMemsetAsync(status_dev, 0, sizeof(int32_t), astream) : hipMemset(status_dev, 0, sizeof(int32_t)));
     if (own_status_host && (s = pinned_word(&status_host))) return s;
@@ -727,7 +726,7 @@ nd_status Net::create(const nd_problem* pr) {
 }
 
 // (Re)build everything that depends on the kernel configuration: the work
-// decomposition, the per-work-item sum buffers and the single-network work map.
+// decomposition and the per-work-item sum buffers.
 nd_status Net::apply_config(const nd_kernel_config& c) {
     quiesce();  // the buffers below may be in use by enqueued work
     drop_graphs();
@@ -740,7 +739,6 @@ nd_status Net::apply_config(const nd_kernel_config& c) {
     release((void*&)tmpl.tsum[0]);
     release((void*&)tmpl.tsum[1]);
     release((void*&)tmpl.rsum);
-    release((void*&)solo_work);
     cfg = c;
     const int64_t n = prob.n;
     if (prob.topo == ND_RING) {
@@ -775,12 +773,6 @@ nd_status Net::apply_config(const nd_kernel_config& c) {
             if ((s = alloc((void**)&tmpl.tsum[b], 2 * (int64_t)tmpl.G * 8))) return s;
         if ((s = alloc((void**)&tmpl.rsum, 2 * (int64_t)tmpl.G * 8))) return s;
     }
-    std::vector<int2> wk;
-    append_work(0, wk);
-    if ((s = alloc((void**)&solo_work, wk.size() * sizeof(int2)))) return s;
-    HIPC(setup_copy(astream, solo_work, wk.data(), wk.size() * sizeof(int2)));
-    int cnt[2] = {(int)wk.size(), 1};
-    HIPC(setup_copy(astream, solo_count, cnt, sizeof cnt));
     return ND_OK;
 }
 
@@ -789,11 +781,6 @@ int64_t Net::work_items() const { return tmpl.G; }
 int Net::shape_key() const {
     if (prob.topo == ND_CSR) return csr_rows(prob.n);
     return prob.topo == ND_CUBE3D || prob.topo == ND_BALL3D || prob.topo == ND_DISK2D ? (int)prob.radius : 0;
-}
-
-void Net::append_work(int desc_index, std::vector<int2>& wk) const {
-    const int64_t m = work_items();
-    for (int64_t t = 0; t < m; ++t) wk.push_back(make_int2(desc_index, (int)t));
 }
 
 nd_status Net::prepare_observe(int64_t steps, const nd_observe* obs, bool may_alloc) {
@@ -1164,9 +1151,10 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
         hipError_t e;
         if (solo) {
             Net* n = nets[idx[0]];
+            // the kernels need no map for one network (work_count, work_at)
             g.desc = n->solo_desc;
-            g.work = n->solo_work;
-            g.nwork = n->solo_count;
+            g.work = nullptr;
+            g.nwork = nullptr;
             if ((e = put_desc(g.desc, n->run_desc(dt[idx[0]], steps[idx[0]]), st)) != hipSuccess)
                 return hip_fail(e, "descriptor upload");
         } else {
