@@ -90,9 +90,10 @@ __device__ __forceinline__ void scatter_plane(const double2* row0, int RW, int q
 }
 
 // Radii up to kBallScatterPairedMaxP are built for two workgroups per CU (at most
-// 128 VGPRs: the 2P+1 running sums of the FP64 inertia model then spill a few
-// words at P = 6, which still measured faster than one workgroup per CU);
-// larger radii keep one workgroup per CU.
+// 128 VGPRs; with the sin/cos coefficients in scalar registers the 2P+1 running sums
+// fit without spills); larger radii keep one workgroup per CU.  100^3 inertia, FP64,
+// us per stage: P = 3 34, P = 4 50, P = 6 82 (halo elements read as y and k_prev and
+// coefficients in vector registers: 38, 53 and 101).
 template <int MODEL, class KT, int P, int STAGE, bool MV>
 __global__ __launch_bounds__(kBallScatterBlock) __attribute__((amdgpu_waves_per_eu(P <= kBallScatterPairedMaxP ? 4 : 2)))
 void k_ball_scatter(const NetDesc* __restrict__ D, const int2* __restrict__ work, const int* __restrict__ nwork_p,
@@ -101,6 +102,7 @@ void k_ball_scatter(const NetDesc* __restrict__ D, const int2* __restrict__ work
     constexpr int V = M::V;
     constexpr int stage = STAGE;
     constexpr int S = 2 * P + 1;
+    constexpr bool kScalarConst = P <= kBallScatterPairedMaxP;  // at the 128-register limit
     extern __shared__ double2 smem[];  // [2][HY][RW] row prefix planes
     __shared__ double lds[2 * kScatterWaves];
     const int nwork = work_count(D, nwork_p);
@@ -157,8 +159,9 @@ void k_ball_scatter(const NetDesc* __restrict__ D, const int2* __restrict__ work
         }
         const int nq = nz + 2 * P;  // planes z0 - P .. z0 + nz - 1 + P
         auto zval = [&](uint32_t i) {
-            const double yy = ld32(y, i);
-            return stage == 1 ? yy : fma(cdt, (double)ld32(kp, i), yy);
+            if constexpr (stage == 1) return ld32(y, i);
+            else if constexpr (kStageValues<KT>) return ld32(kp, i);
+            else return fma(cdt, (double)ld32(kp, i), ld32(y, i));
         };
         double qz[kScatterRows];
         auto load_plane = [&](int q) {
@@ -173,7 +176,7 @@ void k_ball_scatter(const NetDesc* __restrict__ D, const int2* __restrict__ work
             for (int k = 0; k < kScatterRows; ++k) {
                 if (!rv[k]) continue;  // uniform over the wave
                 double z[1] = {qz[k]};
-                double2 m = M::map(z);
+                double2 m = M::template map<kScalarConst>(z);
                 if (!lx) m = make_double2(0.0, 0.0);
                 const double px = wave_incl_scan(m.x), py = wave_incl_scan(m.y);
                 double2* row = pre + (size_t)(wave + k * kScatterWaves) * RW;
@@ -229,22 +232,13 @@ void k_ball_scatter(const NetDesc* __restrict__ D, const int2* __restrict__ work
                     const double2 W = acc_[0];
                     double zz[V];
 #pragma unroll
-                    for (int v = 0; v < V; ++v) zz[v] = stage == 1 ? yv[v] : fma(cdt, kv[v], yv[v]);
-                    const double2 xo = M::map(zz);
+                    for (int v = 0; v < V; ++v) zz[v] = lattice_z<stage, KT>(yv[v], kv[v], cdt);
+                    const double2 xo = M::template map<kScalarConst>(zz);
                     double k[V];
                     M::rhs(d, zz, xo, W, k);
 #pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        const double kk = kq<KT>(k[v]);
-                        if (stage <= 3) st32(gp((KT*)d.k[stage - 1]) + (int64_t)v * n, qi, (KT)kk);
-                        if (stage == 2)
-                            st32(gp(d.acc) + (int64_t)v * n, qi, fma(d.dt3, kk, fma(d.dt6, kv[v], yv[v])));
-                        if (stage == 4) {
-                            const double yo = fma(d.dt6, kk, fma(d.dt3, kv[v], av[v]));
-                            st32(gp(d.y[par ^ 1]) + (int64_t)v * n, qi, yo);
-                            flag_nonfinite(d, yo);
-                        }
-                    }
+                    for (int v = 0; v < V; ++v)
+                        lattice_write<stage, KT>(d, par, (int64_t)v * n, qi, kq<KT>(k[v]), yv[v], kv[v], av[v]);
                     if (stage == 1) {
                         part[0] += xo.x;
                         part[1] += xo.y;

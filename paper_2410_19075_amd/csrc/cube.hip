@@ -12,18 +12,22 @@
 //     (cos z, sin z) plane by plane and keeps the last 2H+1 of them in
 //     registers; the z-direction sum is a running sum (new plane in, oldest
 //     out) in double;
-//   * the z-sums go to LDS; an x-pass (H <= 2: one thread per output column
-//     and halo row, 2H+1 terms; longer windows: sliding along runs of 4
-//     outputs) and a
-//     y-pass (2H+1 terms) finish the cube sum for the cx x cy outputs;
-//   * the RHS and the RK bookkeeping follow the 13-access schedule of the ring
-//     kernels (y double-buffered, k in the bulk type).
-// The coming planes' column values and RK operands are prefetched one to three
-// planes ahead (as registers allow), and the plane loop synchronises through
-// LDS-only barriers so those loads stay in flight.  In FP64 runs (the inertia
-// model up to half-width 2) the three passes work on consecutive planes at once
-// (the z-sums of plane i, the x-pass of plane i-1, the outputs of plane i-2)
-// with one barrier per plane.  All sums are double and every sum has a fixed order.
+//   * the z-sums go to LDS; run threads sum cube_run(H) consecutive windows of
+//     2H+1 along x, others then along y (window_run), and one output thread per
+//     element takes the cube sum, evaluates the RHS and does the RK bookkeeping
+//     (13 accesses per element and step, y double-buffered).
+// The passes work on consecutive planes at once, with one LDS-only barrier per
+// plane.  Bound: the phase between two barriers, i.e. FP64 issue of the column
+// pass (about 60 of 85 vector instructions per halo column and plane) plus the LDS
+// traffic and latency of the runs; with the loads served from L2 the kernel is only
+// 6 % faster, without the runs 35 %.  So each run thread reads 2H+3 entries for
+// three outputs with all reads in flight (a stride of three entries has no bank
+// conflicts; runs of five spill at H = 4: 118 against 87 us), the runs lie on the
+// waves without outputs and come before their column work, and no load or register
+// queue stands inside a branch.  Measured per stage (FP64 / FP32-bulk, 200^3, H = 4):
+// 83 / 67 us; with an x-pass sliding along runs of four, nine LDS reads per output
+// in y and shifted prefetch queues 89 / 77 us.  All sums are double and every sum
+// has a fixed order.
 #include <type_traits>
 
 #include "models.h"
@@ -55,6 +59,50 @@ __device__ __forceinline__ void block_sum_rt(double (&v)[NV], double* lds) {
         v[q] = s;
     }
     __syncthreads();
+}
+
+// R consecutive windows of S entries (entries `is` apart), R <= S: the entries
+// all windows share are added once, the others as suffix and prefix sums, so
+// S + R - 1 entries are read for up to R outputs and nothing is subtracted.
+// Writes the first cnt (reads past them stay inside the LDS arrays).
+template <int S, int R, bool kSplit>
+__device__ __forceinline__ void window_run(const double2* src, int is, double2* dst, int os, int cnt) {
+    double2 v[S + R - 1];
+#pragma unroll
+    for (int e = 0; e < S; ++e) v[e] = src[e * is];
+    double2 core = v[R - 1];
+#pragma unroll
+    for (int e = R; e < S; ++e) {
+        core.x += v[e].x;
+        core.y += v[e].y;
+    }
+#pragma unroll
+    for (int r = R - 3; r >= 0; --r) {  // v[r]: entries r .. R-2
+        v[r].x += v[r + 1].x;
+        v[r].y += v[r + 1].y;
+    }
+    // the other entries only now: all S + R - 1 at once would spill the z ring
+    if (kSplit) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = S; e < S + R - 1; ++e) v[e] = src[e * is];
+#pragma unroll
+    for (int r = 2; r < R; ++r) {  // v[S+r-1]: entries S .. S+r-1
+        v[S + r - 1].x += v[S + r - 2].x;
+        v[S + r - 1].y += v[S + r - 2].y;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        double2 o = core;
+        if (r < R - 1) {
+            o.x += v[r].x;
+            o.y += v[r].y;
+        }
+        if (r > 0) {
+            o.x += v[S + r - 1].x;
+            o.y += v[S + r - 1].y;
+        }
+        if (r < cnt) dst[r * os] = o;
+    }
 }
 
 template <int MODEL, class KT, int H, int STAGE, bool MV>
@@ -107,45 +155,44 @@ __global__ __launch_bounds__(1024) void k_cube_stage(const NetDesc* __restrict__
             if (tid == 0) gp(d.R)[g / d.r_every] = sqrt(s[0] * s[0] + s[1] * s[1]) / (double)n;
         }
 
-        // The plane loop runs in one of two schedules that do the same arithmetic
-        // per output.  Two-phase: the column threads' z-sums of plane i, a
-        // barrier, the x-pass of plane i, a barrier, the y-pass and RHS of plane i
-        // (two LDS buffers per array).  Pipelined (FP64: the one-variable model,
-        // and the inertia model for half-widths up to 2, where registers allow):
-        // in one phase the column threads do plane i, the x-pass plane i-1 and
-        // the output threads plane i-2, then one barrier (three LDS buffers).
-        // Each schedule is written out in full: sharing the passes as lambdas
-        // changed the register allocation and cost FP32-bulk 10 %.
-        constexpr bool kPipe = sizeof(KT) == 8 && (V == 1 || H <= 2);
-        constexpr int NB = kPipe ? 3 : 2;    // LDS buffers per array (cube_lds_buffers)
-        double2* S1 = smem;                  // [NB][HY][HX] z-sums per halo column
-        double2* S0 = S1 + NB * HX * HY;     // [NB][cy][cx] mapped centre values
-        double2* S2 = S0 + NB * cx * cy;     // [NB][HY][cx] x-pass sums
+        // One phase of the plane loop works on four planes at once, then one barrier:
+        //   column threads  plane i      map, z running sum        -> S1, centre -> S0
+        //   x-run threads   plane i - 1  windows along x of S1     -> S2
+        //   y-run threads   plane i - 2  windows along y of S2     -> S3
+        //   output threads  plane i - 3  RHS, RK bookkeeping (S3, S0)
+        constexpr int R = cube_run(H);
+        double2* S1 = smem;                 // [2][HY][HX] z-sums per halo column
+        double2* S2 = S1 + 2 * HX * HY;     // [2][HY][cx] x sums
+        double2* S0 = S2 + 2 * HY * cx;     // [4][cy][cx] mapped centre values
+        double2* S3 = S0 + 4 * cx * cy;     // [2][cy][cx] cube sums
 
         // halo-column thread
         const bool col = tid < HX * HY;
         const int hx = col ? tid % HX : 0, hy = col ? tid / HX : 0;
         const bool inner = col && hx >= H && hx < H + cx && hy >= H && hy < H + cy;
+        const int ctr = inner ? (hy - H) * cx + (hx - H) : 0;
         const uint32_t colbase = (uint32_t)wrapm(x0 - H + hx, n1) + (uint32_t)n1 * (uint32_t)wrapm(y0 - H + hy, n2);
         // output thread
         const bool outv = tid < cx * cy && (tid % cx) < ex && (tid / cx) < ey;
         const int ox = outv ? tid % cx : 0, oy = outv ? tid / cx : 0;
         const uint32_t obase = (uint32_t)(x0 + ox) + (uint32_t)n1 * (uint32_t)(y0 + oy);
-        // x-pass thread. Short windows (H <= 2): one output column of one halo
-        // row (HY * cx <= HX * HY threads), consecutive lanes on consecutive LDS
-        // entries. Longer windows: a run of up to kRunX consecutive outputs of
-        // one row, sliding the window along it (fewer LDS reads per output).
-        constexpr bool kDirectX = H <= 2;
-        constexpr int kRunX = 4;
-        const int nsx = (cx + kRunX - 1) / kRunX;
-        const bool xr = kDirectX ? tid < HY * cx : tid < HY * nsx;
-        const int xrow = xr ? (kDirectX ? tid / cx : tid / nsx) : 0;
-        const int xs0 = xr ? (kDirectX ? tid - xrow * cx : (tid - xrow * nsx) * kRunX) : 0;
-        const int xcnt = kDirectX ? 1 : (xr ? min(kRunX, cx - xs0) : 0);
+        // run threads: the waves behind the output threads first, so that the waves
+        // with output work do not also carry the runs
+        const int nsx = (cx + R - 1) / R, nsy = (cy + R - 1) / R;
+        const int bs = blockDim.x;
+        const int xoff = ((cx * cy + kWave - 1) & ~(kWave - 1)) % bs;
+        const int yoff = (xoff + ((HY * nsx + kWave - 1) & ~(kWave - 1))) % bs;
+        const int xt = tid - xoff + (tid < xoff ? bs : 0), yt = tid - yoff + (tid < yoff ? bs : 0);
+        const bool xr = xt < HY * nsx, yr = yt < nsy * cx;
+        const int xrow = xr ? xt / nsx : 0, xs0 = xr ? (xt - xrow * nsx) * R : 0;
+        const int xsrc = xrow * HX + xs0, xdst = xrow * cx + xs0, xcnt = min(R, cx - xs0);
+        const int yrow = yr ? yt / cx : 0;
+        const int ysrc = yr ? yrow * R * cx + (yt - yrow * cx) : 0, ycnt = min(R, cy - yrow * R);
 
         auto zval = [&](uint32_t i) {
-            const double yy = ld32(y, i);
-            return stage == 1 ? yy : fma(cdt, (double)ld32(kp, i), yy);
+            if constexpr (stage == 1) return ld32(y, i);
+            else if constexpr (kStageValues<KT>) return ld32(kp, i);
+            else return fma(cdt, (double)ld32(kp, i), ld32(y, i));
         };
         // the last 2H+1 mapped planes of this column; in the bulk type, which is
         // exact (FP32-bulk maps are computed in float)
@@ -162,283 +209,96 @@ __global__ __launch_bounds__(1024) void k_cube_stage(const NetDesc* __restrict__
 #pragma unroll
         for (int u = 0; u < 2 * H; ++u) {
             double z[1] = {zval(colbase + plane * (uint32_t)wrapm(z0 - H + u, n3))};
-            rb[u] = to_rb(M::map(z));
+            rb[u] = to_rb(M::template map<true>(z));
             zsx += (double)rb[u].x;
             zsy += (double)rb[u].y;
         }
         rb[2 * H] = to_rb(make_double2(0.0, 0.0));
         double part[2] = {0.0, 0.0};  // stage 1: sums of map(y) for R
-        if constexpr (!kPipe) {
-            // two-phase schedule; prefetched operands PF planes ahead (a shift
-            // queue with static indices): the column value of the plane entering
-            // the z window and the RK operands of the output plane, as far ahead as
-            // 128 VGPRs allow: three planes in FP32-bulk for the one-variable model;
-            // the inertia model (its psi operands besides) one in FP64, two in FP32-bulk
-            constexpr int PF = V == 1 ? 3 : (sizeof(KT) == 8 ? 1 : 2);
-            double qy[PF], qk[PF], qry[PF], qrk[PF], qra[PF];
-            auto fetch = [&](int ahead, double& cy_, double& ck_, double& ry_, double& rk_, double& ra_) {
-                // operands of output plane z0 + ahead (clamped inside this work item)
-                const int zo_ = z0 + min(ahead, nz - 1);
-                const uint32_t ci = colbase + plane * (uint32_t)wrapm(zo_ + H, n3);
-                cy_ = ld32(y, ci);
-                ck_ = stage != 1 ? (double)ld32(kp, ci) : 0.0;
-                const uint32_t oi = obase + plane * (uint32_t)zo_;
-                ry_ = ld32(y, oi);
-                rk_ = (stage == 2 || stage == 4) ? (double)ld32(kp, oi) : 0.0;
-                ra_ = stage == 4 ? ld32(acc, oi) : 0.0;
-            };
+        // Prefetched operands: the column value of the next plane and the RK operands
+        // of the next output plane, one phase ahead (three planes ahead measured the
+        // same).  The loads stand outside every branch: a conditional load, or a queue
+        // shifted by moves, makes the compiler wait for the newest load in every phase.
+        constexpr bool kTwo = stage != 1 && !kStageValues<KT>;  // a column value is y and k_prev
+        double qy;
+        KT qk;
+        int zin = wrapm(z0 + H, n3), zcol = 0;  // plane the next column fetch reads; columns fetched
+        auto fetch_col = [&](double& v, KT& k) {
+            const uint32_t ci = colbase + plane * (uint32_t)zin;
+            if constexpr (stage == 1 || kTwo) v = ld32(y, ci);
+            else v = (double)ld32(kp, ci);
+            if constexpr (kTwo) k = ld32(kp, ci);
+            if (++zcol < nz) zin = zin + 1 == n3 ? 0 : zin + 1;  // past the last plane: that one again
+        };
+        double ry[V], ra[V];
+        KT rk[V];
+        auto fetch_rk = [&](int io) {
+            const uint32_t oi = obase + plane * (uint32_t)(z0 + min(max(io, 0), nz - 1));
 #pragma unroll
-            for (int f = 0; f < PF; ++f) fetch(f, qy[f], qk[f], qry[f], qrk[f], qra[f]);
-            for (int zb = 0; zb < nz; zb += S) {
-#pragma unroll
-                for (int u = 0; u < S; ++u) {
-                    if (zb + u < nz) {
-                        const int zo = z0 + zb + u;
-                        const double zc = stage == 1 ? qy[0] : fma(cdt, qk[0], qy[0]);
-                        const double cry = qry[0], crk = qrk[0], cra = qra[0];
-#pragma unroll
-                        for (int f = 0; f + 1 < PF; ++f) {
-                            qy[f] = qy[f + 1];
-                            qk[f] = qk[f + 1];
-                            qry[f] = qry[f + 1];
-                            qrk[f] = qrk[f + 1];
-                            qra[f] = qra[f + 1];
-                        }
-                        fetch(zb + u + PF, qy[PF - 1], qk[PF - 1], qry[PF - 1], qrk[PF - 1], qra[PF - 1]);
-                        // z window of output plane zo: planes zo-H .. zo+H; the new
-                        // plane enters the running sum, the oldest leaves it after
-                        {
-                            double z[1] = {zc};
-                            rb[(u + 2 * H) % S] = to_rb(M::map(z));
-                        }
-                        const double2 sz = make_double2(zsx + (double)rb[(u + 2 * H) % S].x,
-                                                        zsy + (double)rb[(u + 2 * H) % S].y);
-                        zsx = sz.x - (double)rb[u % S].x;
-                        zsy = sz.y - (double)rb[u % S].y;
-                        const int buf = (zb + u) & 1;
-                        if (col) S1[buf * HX * HY + tid] = sz;
-                        if (inner)
-                            S0[buf * cx * cy + (hy - H) * cx + (hx - H)] =
-                                make_double2((double)rb[(u + H) % S].x, (double)rb[(u + H) % S].y);
-                        lds_barrier();
-                        // x-pass over the HY rows
-                        if (xr) {
-                            const double2* src = S1 + buf * HX * HY + xrow * HX + xs0;
-                            double2* dst = S2 + buf * HY * cx + xrow * cx + xs0;
-                            double2 a = make_double2(0.0, 0.0);
-#pragma unroll
-                            for (int dx = 0; dx < S; ++dx) {
-                                a.x += src[dx].x;
-                                a.y += src[dx].y;
-                            }
-                            dst[0] = a;
-                            if constexpr (!kDirectX) {
-#pragma unroll
-                                for (int r = 1; r < kRunX; ++r) {
-                                    if (r < xcnt) {
-                                        const double2 in = src[r + 2 * H], out = src[r - 1];
-                                        a.x = (a.x + in.x) - out.x;
-                                        a.y = (a.y + in.y) - out.y;
-                                        dst[r] = a;
-                                    }
-                                }
-                            }
-                        }
-                        lds_barrier();
-                        // y-pass, RHS, RK bookkeeping
-                        if (outv) {
-                            const double2* src = S2 + buf * HY * cx + oy * cx + ox;
-                            double2 bsum = make_double2(0.0, 0.0);
-#pragma unroll
-                            for (int dy = 0; dy < S; ++dy) {
-                                bsum.x += src[dy * cx].x;
-                                bsum.y += src[dy * cx].y;
-                            }
-                            const double2 xo = S0[buf * cx * cy + oy * cx + ox];
-                            const double2 W = make_double2(bsum.x - xo.x, bsum.y - xo.y);
-                            const uint32_t q = obase + plane * (uint32_t)zo;
-                            // variable 1 (psi, inertia only): operands read here, not prefetched
-                            double y1 = 0.0, kp1 = 0.0, a1 = 0.0;
-                            double zz[V];
-                            zz[0] = 0.0;  // the phase enters through xo
-                            if constexpr (V == 2) {
-                                y1 = ld32(y + n, q);
-                                kp1 = stage != 1 ? (double)ld32(kp + n, q) : 0.0;
-                                a1 = stage == 4 ? ld32(acc + n, q) : 0.0;
-                                zz[V - 1] = stage == 1 ? y1 : fma(cdt, kp1, y1);
-                            }
-                            double k[V];
-                            M::rhs(d, zz, xo, W, k);
-                            const double kk = kq<KT>(k[0]);
-                            if constexpr (V == 2) {
-                                const double kk1 = kq<KT>(k[1]);
-                                if (stage <= 3) st32(gp((KT*)d.k[stage - 1]) + n, q, (KT)kk1);
-                                if (stage == 2) st32(gp(d.acc) + n, q, fma(d.dt3, kk1, fma(d.dt6, kp1, y1)));
-                                if (stage == 4) {
-                                    const double yo1 = fma(d.dt6, kk1, fma(d.dt3, kp1, a1));
-                                    st32(gp(d.y[par ^ 1]) + n, q, yo1);
-                                    flag_nonfinite(d, yo1);
-                                }
-                            }
-                            if (stage == 1) {
-                                st32(gp((KT*)d.k[0]), q, (KT)kk);
-                                part[0] += xo.x;
-                                part[1] += xo.y;
-                                if (MV && (d.obs & OBS_MV) && g == d.mv_start) st32(gp(d.mv), q, cry);
-                            } else if (stage == 2) {
-                                st32(gp((KT*)d.k[1]), q, (KT)kk);
-                                st32(gp(d.acc), q, fma(d.dt3, kk, fma(d.dt6, crk, cry)));
-                            } else if (stage == 3) {
-                                st32(gp((KT*)d.k[2]), q, (KT)kk);
-                            } else {
-                                const double yo = fma(d.dt6, kk, fma(d.dt3, crk, cra));
-                                st32(gp(d.y[par ^ 1]), q, yo);
-                                flag_nonfinite(d, yo);
-                            }
-                        }
-                    }
-                }
+            for (int v = 0; v < V; ++v) {
+                ry[v] = ld32(y + (int64_t)v * n, oi);
+                if constexpr (stage == 2 || stage == 4) rk[v] = ld32(kp + (int64_t)v * n, oi);
+                else if (stage == 3 && v > 0) rk[v] = ld32(kp + (int64_t)v * n, oi);
+                if constexpr (stage == 4) ra[v] = ld32(acc + (int64_t)v * n, oi);
             }
-        } else {
-            // pipelined schedule: column values PF planes ahead of the column
-            // pass, RK operands PF planes ahead of the output pass (two planes in
-            // stages 1 and 3, one in 2 and 4, within 128 VGPRs)
-            constexpr int PF = (STAGE == 1 || STAGE == 3) ? 2 : 1;
-            double qy[PF], qk[PF], qry[PF], qrk[PF], qra[PF];
-            auto fetch_col = [&](int ahead, double& cy_, double& ck_) {
-                const int zo_ = z0 + min(ahead, nz - 1);
-                const uint32_t ci = colbase + plane * (uint32_t)wrapm(zo_ + H, n3);
-                cy_ = ld32(y, ci);
-                ck_ = stage != 1 ? (double)ld32(kp, ci) : 0.0;
-            };
-            auto fetch_rk = [&](int ahead, double& ry_, double& rk_, double& ra_) {
-                const int zo_ = z0 + min(ahead, nz - 1);
-                const uint32_t oi = obase + plane * (uint32_t)zo_;
-                ry_ = ld32(y, oi);
-                rk_ = (stage == 2 || stage == 4) ? (double)ld32(kp, oi) : 0.0;
-                ra_ = stage == 4 ? ld32(acc, oi) : 0.0;
-            };
+        };
+        fetch_col(qy, qk);
+        fetch_rk(0);
+        const int nit = nz + 3;
+        for (int zb = 0; zb < nit; zb += S) {
 #pragma unroll
-            for (int f = 0; f < PF; ++f) fetch_col(f, qy[f], qk[f]);
-#pragma unroll
-            for (int f = 0; f < PF; ++f) fetch_rk(f, qry[f], qrk[f], qra[f]);
-            const int nit = nz + 2;
-            for (int zb = 0; zb < nit; zb += S) {
-#pragma unroll
-                for (int u = 0; u < S; ++u) {
-                    const int i = zb + u;
-                    if (i >= nit) continue;  // uniform
-                    if (i < nz) {  // column pass, plane i
-                        const double zc = stage == 1 ? qy[0] : fma(cdt, qk[0], qy[0]);
-#pragma unroll
-                        for (int f = 0; f + 1 < PF; ++f) {
-                            qy[f] = qy[f + 1];
-                            qk[f] = qk[f + 1];
-                        }
-                        fetch_col(i + PF, qy[PF - 1], qk[PF - 1]);
-                        {
-                            double z[1] = {zc};
-                            rb[(u + 2 * H) % S] = to_rb(M::map(z));
-                        }
-                        const double2 sz = make_double2(zsx + (double)rb[(u + 2 * H) % S].x,
-                                                        zsy + (double)rb[(u + 2 * H) % S].y);
-                        zsx = sz.x - (double)rb[u % S].x;
-                        zsy = sz.y - (double)rb[u % S].y;
-                        const int buf = i % NB;
-                        if (col) S1[buf * HX * HY + tid] = sz;
-                        if (inner)
-                            S0[buf * cx * cy + (hy - H) * cx + (hx - H)] =
-                                make_double2((double)rb[(u + H) % S].x, (double)rb[(u + H) % S].y);
-                    }
-                    if (i >= 1 && i - 1 < nz) {  // x-pass over the HY rows, plane i - 1
-                        const int buf = (i - 1) % NB;
-                        if (xr) {
-                            const double2* src = S1 + buf * HX * HY + xrow * HX + xs0;
-                            double2* dst = S2 + buf * HY * cx + xrow * cx + xs0;
-                            double2 a = make_double2(0.0, 0.0);
-#pragma unroll
-                            for (int dx = 0; dx < S; ++dx) {
-                                a.x += src[dx].x;
-                                a.y += src[dx].y;
-                            }
-                            dst[0] = a;
-                            if constexpr (!kDirectX) {
-#pragma unroll
-                                for (int r = 1; r < kRunX; ++r) {
-                                    if (r < xcnt) {
-                                        const double2 in = src[r + 2 * H], out = src[r - 1];
-                                        a.x = (a.x + in.x) - out.x;
-                                        a.y = (a.y + in.y) - out.y;
-                                        dst[r] = a;
-                                    }
-                                }
-                            }
-                        }
-                    }
-                    if (i >= 2) {                                    // output plane i - 2
-                        const int io = i - 2;
-                        const double cry = qry[0], crk = qrk[0], cra = qra[0];
-#pragma unroll
-                        for (int f = 0; f + 1 < PF; ++f) {
-                            qry[f] = qry[f + 1];
-                            qrk[f] = qrk[f + 1];
-                            qra[f] = qra[f + 1];
-                        }
-                        fetch_rk(io + PF, qry[PF - 1], qrk[PF - 1], qra[PF - 1]);
-                        const int zo = z0 + io, buf = io % NB;
-                        if (outv) {
-                            const double2* src = S2 + buf * HY * cx + oy * cx + ox;
-                            double2 bsum = make_double2(0.0, 0.0);
-#pragma unroll
-                            for (int dy = 0; dy < S; ++dy) {
-                                bsum.x += src[dy * cx].x;
-                                bsum.y += src[dy * cx].y;
-                            }
-                            const double2 xo = S0[buf * cx * cy + oy * cx + ox];
-                            const double2 W = make_double2(bsum.x - xo.x, bsum.y - xo.y);
-                            const uint32_t q = obase + plane * (uint32_t)zo;
-                            // variable 1 (psi, inertia only): operands read here, not prefetched
-                            double y1 = 0.0, kp1 = 0.0, a1 = 0.0;
-                            double zz[V];
-                            zz[0] = 0.0;  // the phase enters through xo
-                            if constexpr (V == 2) {
-                                y1 = ld32(y + n, q);
-                                kp1 = stage != 1 ? (double)ld32(kp + n, q) : 0.0;
-                                a1 = stage == 4 ? ld32(acc + n, q) : 0.0;
-                                zz[V - 1] = stage == 1 ? y1 : fma(cdt, kp1, y1);
-                            }
-                            double k[V];
-                            M::rhs(d, zz, xo, W, k);
-                            const double kk = kq<KT>(k[0]);
-                            if constexpr (V == 2) {
-                                const double kk1 = kq<KT>(k[1]);
-                                if (stage <= 3) st32(gp((KT*)d.k[stage - 1]) + n, q, (KT)kk1);
-                                if (stage == 2) st32(gp(d.acc) + n, q, fma(d.dt3, kk1, fma(d.dt6, kp1, y1)));
-                                if (stage == 4) {
-                                    const double yo1 = fma(d.dt6, kk1, fma(d.dt3, kp1, a1));
-                                    st32(gp(d.y[par ^ 1]) + n, q, yo1);
-                                    flag_nonfinite(d, yo1);
-                                }
-                            }
-                            if (stage == 1) {
-                                st32(gp((KT*)d.k[0]), q, (KT)kk);
-                                part[0] += xo.x;
-                                part[1] += xo.y;
-                                if (MV && (d.obs & OBS_MV) && g == d.mv_start) st32(gp(d.mv), q, cry);
-                            } else if (stage == 2) {
-                                st32(gp((KT*)d.k[1]), q, (KT)kk);
-                                st32(gp(d.acc), q, fma(d.dt3, kk, fma(d.dt6, crk, cry)));
-                            } else if (stage == 3) {
-                                st32(gp((KT*)d.k[2]), q, (KT)kk);
-                            } else {
-                                const double yo = fma(d.dt6, kk, fma(d.dt3, crk, cra));
-                                st32(gp(d.y[par ^ 1]), q, yo);
-                                flag_nonfinite(d, yo);
-                            }
-                        }
-                    }
-                    lds_barrier();
+            for (int u = 0; u < S; ++u) {
+                const int i = zb + u;
+                if (i >= nit) break;  // uniform
+                if (xr && i >= 1 && i - 1 < nz) {
+                    const int b = (i - 1) & 1;
+                    window_run<S, R, (H >= 4 && sizeof(KT) == 8)>(S1 + b * HX * HY + xsrc, 1, S2 + b * HY * cx + xdst, 1, xcnt);
                 }
+                if (yr && i >= 2 && i - 2 < nz) {
+                    const int b = i & 1;
+                    window_run<S, R, (H >= 4 && sizeof(KT) == 8)>(S2 + b * HY * cx + ysrc, cx, S3 + b * cx * cy + ysrc, cx, ycnt);
+                }
+                double z[1] = {kTwo ? fma(cdt, (double)qk, qy) : qy};
+                fetch_col(qy, qk);
+                if (i < nz) {  // column pass, plane i
+                    // z window of plane i: planes i-H .. i+H; the new plane enters the
+                    // running sum, the oldest leaves it after
+                    rb[(u + 2 * H) % S] = to_rb(M::template map<true>(z));
+                    const double2 sz = make_double2(zsx + (double)rb[(u + 2 * H) % S].x,
+                                                    zsy + (double)rb[(u + 2 * H) % S].y);
+                    zsx = sz.x - (double)rb[u % S].x;
+                    zsy = sz.y - (double)rb[u % S].y;
+                    if (col) S1[(i & 1) * HX * HY + tid] = sz;
+                    if (inner)
+                        S0[(i & 3) * cx * cy + ctr] = make_double2((double)rb[(u + H) % S].x, (double)rb[(u + H) % S].y);
+                }
+                double cry[V], crk[V], cra[V];
+#pragma unroll
+                for (int v = 0; v < V; ++v) {
+                    cry[v] = ry[v];
+                    crk[v] = (stage == 2 || stage == 4 || (stage == 3 && v > 0)) ? (double)rk[v] : 0.0;
+                    cra[v] = stage == 4 ? ra[v] : 0.0;
+                }
+                if (i >= 3 && outv) {  // output plane i - 3
+                    const int io = i - 3, q0 = oy * cx + ox;
+                    const double2 bsum = S3[(io & 1) * cx * cy + q0], xo = S0[(io & 3) * cx * cy + q0];
+                    const double2 W = make_double2(bsum.x - xo.x, bsum.y - xo.y);
+                    const uint32_t q = obase + plane * (uint32_t)(z0 + io);
+                    double zz[V], k[V];
+                    zz[0] = 0.0;  // the phase enters through xo
+                    if constexpr (V == 2) zz[V - 1] = lattice_z<stage, KT>(cry[V - 1], crk[V - 1], cdt);
+                    M::rhs(d, zz, xo, W, k);
+#pragma unroll
+                    for (int v = 0; v < V; ++v)
+                        lattice_write<stage, KT>(d, par, (int64_t)v * n, q, kq<KT>(k[v]), cry[v], crk[v], cra[v]);
+                    if (stage == 1) {
+                        part[0] += xo.x;
+                        part[1] += xo.y;
+                        if (MV && (d.obs & OBS_MV) && g == d.mv_start) st32(gp(d.mv), q, cry[0]);
+                    }
+                }
+                fetch_rk(i - 2);
+                lds_barrier();
             }
         }
         if (stage == 1) {
@@ -552,8 +412,9 @@ __global__ __launch_bounds__(BS) void k_ball_stage(const NetDesc* __restrict__ D
             rowbase[k] = xcol + (uint32_t)n1 * (uint32_t)wrapm(y0 - P + (rv[k] ? r : 0), n2);
         }
         auto zval = [&](uint32_t i) {
-            const double yy = ld32(y, i);
-            return stage == 1 ? yy : fma(cdt, (double)ld32(kp, i), yy);
+            if constexpr (stage == 1) return ld32(y, i);
+            else if constexpr (kStageValues<KT>) return ld32(kp, i);
+            else return fma(cdt, (double)ld32(kp, i), ld32(y, i));
         };
         // map plane q (relative: absolute z = z0 - P + q) into ring slot q % NS
         double qz[kBallRowsPerWave];
@@ -644,21 +505,13 @@ __global__ __launch_bounds__(BS) void k_ball_stage(const NetDesc* __restrict__ D
                 }
                 double zz[V];
 #pragma unroll
-                for (int v = 0; v < V; ++v) zz[v] = stage == 1 ? yv[v] : fma(cdt, kv[v], yv[v]);
+                for (int v = 0; v < V; ++v) zz[v] = lattice_z<stage, KT>(yv[v], kv[v], cdt);
                 const double2 xo = M::map(zz);
                 double k[V];
                 M::rhs(d, zz, xo, W, k);
 #pragma unroll
-                for (int v = 0; v < V; ++v) {
-                    const double kk = kq<KT>(k[v]);
-                    if (stage <= 3) st32(gp((KT*)d.k[stage - 1]) + (int64_t)v * n, q, (KT)kk);
-                    if (stage == 2) st32(gp(d.acc) + (int64_t)v * n, q, fma(d.dt3, kk, fma(d.dt6, kv[v], yv[v])));
-                    if (stage == 4) {
-                        const double yo = fma(d.dt6, kk, fma(d.dt3, kv[v], av[v]));
-                        st32(gp(d.y[par ^ 1]) + (int64_t)v * n, q, yo);
-                        flag_nonfinite(d, yo);
-                    }
-                }
+                for (int v = 0; v < V; ++v)
+                    lattice_write<stage, KT>(d, par, (int64_t)v * n, q, kq<KT>(k[v]), yv[v], kv[v], av[v]);
                 if (stage == 1) {
                     part[0] += xo.x;
                     part[1] += xo.y;
@@ -810,13 +663,9 @@ bool cube_select(int model, int prec, int h, CubeLaunch* out) {
     return false;
 }
 
-int cube_lds_buffers(int model, int prec, int h) {
-    return prec == ND_FP64 && (model == ND_KURAMOTO || h <= 2) ? 3 : 2;
-}
-
-size_t cube_smem_bytes(int h, int cx, int cy, int nb) {
-    const size_t HX = cx + 2 * h, HY = cy + 2 * h;
-    return (nb * HX * HY + nb * (size_t)cx * cy + nb * HY * cx) * sizeof(double2);
+size_t cube_smem_bytes(int h, int cx, int cy) {
+    const size_t HX = cx + 2 * h, HY = cy + 2 * h, out = (size_t)cx * cy;
+    return (2 * HX * HY + 2 * HY * cx + 6 * out) * sizeof(double2);
 }
 
 int cube_block(int h, int cx, int cy) {

@@ -13,6 +13,18 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t m) {
     return __longlong_as_double(__double_as_longlong(v) ^ ((long long)(m & 0x80000000u) << 32));
 }
 
+// A double constant, with SC held in a scalar register pair the FMA reads it from.
+// Left to itself the compiler keeps polynomial coefficients in vector registers:
+// about 20 of them, which the kernels at the 128-register limit do not have (ball
+// P = 6: spills, 90 against 82 us per stage; the cube's plane loop). Elsewhere the
+// scalar moves cost more than the registers (ball P = 8 63 against 67 us, one ring
+// of 1024 0.93 against 0.97 us per stage).
+template <bool SC>
+__device__ __forceinline__ double sconst(double c) {
+    if constexpr (SC) asm("" : "+s"(c));
+    return c;
+}
+
 // sin and cos of one double: Cody-Waite reduction by pi/2 (two-part constant,
 // each part subtracted with one fused multiply-add), then minimax polynomials of
 // sin and cos on [-pi/4, pi/4] of degrees 13 and 14 (fitted by the Remez
@@ -29,24 +41,23 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t m) {
 // degrees more: 1.44e-16 and 3.20e-17).  Bound: FP64 issue of the callers; this
 // form takes 20 FP64 operations, the Taylor form with the quadrant by floor and
 // conversion took 24.  Inf and NaN give NaN.
+template <bool SC = false>
 __device__ __forceinline__ void sincos_cw(double x, double* sp, double* cp) {
     const double q = rint(x * 0.63661977236758134308);          // x / (pi/2), nearest
     const double r1 = fma(-q, 1.5707963267948966192, x);        // pi/2 rounded to double
     const double r = fma(-q, 6.123233995736766036e-17, r1);     // pi/2 minus that
     const double r2 = r * r;
-    double ps = 1.588805743874414e-10;
-    ps = fma(ps, r2, -2.5050590858861764e-08);
-    ps = fma(ps, r2, 2.7557312482336066e-06);
-    ps = fma(ps, r2, -0.00019841269825742673);
-    ps = fma(ps, r2, 0.008333333333316218);
-    ps = fma(ps, r2, -0.166666666666666);
+    double ps = fma(sconst<SC>(1.588805743874414e-10), r2, sconst<SC>(-2.5050590858861764e-08));
+    ps = fma(ps, r2, sconst<SC>(2.7557312482336066e-06));
+    ps = fma(ps, r2, sconst<SC>(-0.00019841269825742673));
+    ps = fma(ps, r2, sconst<SC>(0.008333333333316218));
+    ps = fma(ps, r2, sconst<SC>(-0.166666666666666));
     const double sn = fma(r * r2, ps, r);
-    double pc = -1.1359934247561652e-11;
-    pc = fma(pc, r2, 2.087572928127532e-09);
-    pc = fma(pc, r2, -2.75573144010307e-07);
-    pc = fma(pc, r2, 2.4801587289671537e-05);
-    pc = fma(pc, r2, -0.0013888888888874474);
-    pc = fma(pc, r2, 0.0416666666666666);
+    double pc = fma(sconst<SC>(-1.1359934247561652e-11), r2, sconst<SC>(2.087572928127532e-09));
+    pc = fma(pc, r2, sconst<SC>(-2.75573144010307e-07));
+    pc = fma(pc, r2, sconst<SC>(2.4801587289671537e-05));
+    pc = fma(pc, r2, sconst<SC>(-0.0013888888888874474));
+    pc = fma(pc, r2, sconst<SC>(0.0416666666666666));
     pc = fma(pc, r2, -0.5);
     const double cs = fma(r2, pc, 1.0);
     const uint32_t f = (uint32_t)((unsigned long long)__double_as_longlong(__builtin_amdgcn_fract(q * 0.25)) >> 32);
@@ -76,10 +87,11 @@ struct RingModel;
 template <class KT>
 struct RingModel<ND_KURAMOTO, KT> {
     static constexpr int V = 1;
+    template <bool SC = false>
     __device__ static __forceinline__ double2 map(const double* z) {
         double s, c;
         if constexpr (sizeof(KT) == 8) {
-            sincos_cw(z[0], &s, &c);
+            sincos_cw<SC>(z[0], &s, &c);
         } else {
             // bulk float: reduce to revolutions in double, then the hardware
             // sin/cos (their argument is in revolutions)
@@ -114,7 +126,10 @@ struct RingModel<ND_KURAMOTO, KT> {
 template <class KT>
 struct RingModel<ND_KURAMOTO_INERTIA, KT> {
     static constexpr int V = 2;
-    __device__ static __forceinline__ double2 map(const double* z) { return RingModel<ND_KURAMOTO, KT>::map(z); }
+    template <bool SC = false>
+    __device__ static __forceinline__ double2 map(const double* z) {
+        return RingModel<ND_KURAMOTO, KT>::template map<SC>(z);
+    }
     template <class D>
     __device__ static __forceinline__ void rhs(const D& d, const double* z, double2 xo, double2 W, double* k) {
         double force[1];
@@ -166,6 +181,56 @@ struct RingModel<ND_FHN, KT> {
 template <class KT>
 __device__ __forceinline__ double kq(double k) {
     return (double)(KT)k;  // the value that is stored (and that every reader sees)
+}
+
+// Lattice stage kernels, FP64: the three buffers d.k hold the stage values z2, z3,
+// z4 instead of the slopes.  A halo element is then one load in every stage (with
+// the slopes it is y and k_prev in stages 2 to 4), and the step is completed from
+// the differences to y:
+//   stage 1: reads y             writes z2 = y + dt/2 k1
+//   stage 2: reads y, z2         writes z3 = y + dt/2 k2, acc = (z2 - y) + 2 (z3 - y)
+//   stage 3: reads y, z3         writes z4 = y + dt k3
+//   stage 4: reads y, z4, acc    writes y' = y + dt/6 k4 + (acc + (z4 - y)) / 3
+// the same 13 accesses per element and step.  The differences are exact or small,
+// so y' has one rounding at the scale of y besides those of z2 .. z4 (weights 1/3,
+// 2/3, 1/3), fewer than the slope form's four.  FP32-bulk keeps slopes: stored
+// in float they are half the bytes of a stage value.
+template <class KT>
+constexpr bool kStageValues = sizeof(KT) == 8;
+
+// Value read for the stage input at an element: v the d.k entry (stages 2 to 4), y the state.
+template <int STAGE, class KT>
+__device__ __forceinline__ double lattice_z(double y, double v, double cdt) {
+    if (STAGE == 1) return y;
+    return kStageValues<KT> ? v : fma(cdt, v, y);
+}
+
+// What stage STAGE writes for one variable of one element: slope kk, own state y,
+// own d.k entry v (stages 2 and 4), own acc (stage 4); q the element, `off` the
+// variable's offset.  Returns the new state in stage 4.
+template <int STAGE, class KT>
+__device__ __forceinline__ double lattice_write(const NetDesc& d, int par, int64_t off, uint32_t q, double kk, double y,
+                                                double v, double acc) {
+    if constexpr (kStageValues<KT>) {
+        if (STAGE <= 3) {
+            const double z = fma(STAGE == 3 ? d.dt : 0.5 * d.dt, kk, y);
+            st32(gp((double*)d.k[STAGE - 1 < 3 ? STAGE - 1 : 0]) + off, q, z);
+            if (STAGE == 2) st32(gp(d.acc) + off, q, fma(2.0, z - y, v - y));
+            return 0.0;
+        }
+        const double yo = y + fma(d.dt6, kk, (acc + (v - y)) * (1.0 / 3.0));
+        st32(gp(d.y[par ^ 1]) + off, q, yo);
+        flag_nonfinite(d, yo);
+        return yo;
+    } else {
+        if (STAGE <= 3) st32(gp((KT*)d.k[STAGE - 1 < 3 ? STAGE - 1 : 0]) + off, q, (KT)kk);
+        if (STAGE == 2) st32(gp(d.acc) + off, q, fma(d.dt3, kk, fma(d.dt6, v, y)));
+        if (STAGE <= 3) return 0.0;
+        const double yo = fma(d.dt6, kk, fma(d.dt3, v, acc));
+        st32(gp(d.y[par ^ 1]) + off, q, yo);
+        flag_nonfinite(d, yo);
+        return yo;
+    }
 }
 
 // Stage value z_v(idx) = y + c dt k_prev (stage 1: y).  Written once here so the

@@ -289,28 +289,44 @@ int device_cu_count() {
     return cus;
 }
 
-// Cube tiling.  One workgroup of (cx+2h)(cy+2h) column threads holds a CU, and
-// the time of a stage is about (rounds of workgroups over the CUs) x (planes
-// per work item, including the 2h lead-in) x (threads per workgroup), so the
-// tiling minimising that product is taken (ties: fewer halo columns, then
-// wider x for coalescing).
+// Cube tiling.  A work item of cz planes takes a launch and lead-in share, 2h
+// planes of mapping, and cz + 3 phases of the pipelined plane loop; a phase takes
+// about 0.4 us plus 0.05 us per wave resident on the CU (its barrier and LDS round
+// trips, then the waves' issue): measured 0.55 us at 3 waves, 0.72 at 6, 1.1 at 13,
+// 1.15 at 15, a tenth less where two or more work items share a CU (they fill each
+// other's waits).  Up to 16 waves (128 VGPRs) and the LDS of a CU are shared by its work
+// items, which run in rounds.  Tiles whose extents the run length does not divide
+// pay for the idle part of the last run.  Rounds x threads alone (the rule before)
+// took few long work items on small lattices: us per stage (that rule and the loop
+// it was made for / now) 40^3 h = 4 12.4 / 8.0, 31 x 37 x 29 h = 2 9.5 / 6.1, 101 x 90
+// x 77 h = 2 FP32-bulk 16.5 / 12.9.
 static void cube_tiles(const nd_problem* p, int cus, int* cx_, int* cy_, int* cz_) {
     const int h = (int)p->radius;
     const int n1 = (int)p->n1, n2 = (int)p->n2, n3 = (int)p->n3;
+    const int run = cube_run(h);
     double best = 1e300;
     *cx_ = 1, *cy_ = 1, *cz_ = n3;
     for (int cx = 1; cx <= std::min(n1, 64); ++cx) {
         for (int cy = 1; cy <= std::min(n2, 64); ++cy) {
             const int halo = (cx + 2 * h) * (cy + 2 * h);
             if (halo > 1024) break;
-            const int64_t threads = (halo + 63) / 64 * 64;
+            const int waves = (halo + 63) / 64;
+            const size_t smem = cube_smem_bytes(h, cx, cy);
+            const int per_cu = std::max(1, std::min(16 / waves, (int)(kBallSmemMax / smem)));
             const int64_t tiles = (int64_t)((n1 + cx - 1) / cx) * ((n2 + cy - 1) / cy);
+            // share of the run threads' work that is kept
+            const double fill = (double)cx * cy / (((cx + run - 1) / run * run) * (double)((cy + run - 1) / run * run));
             for (int zt = 1; zt <= std::min(n3, 256); ++zt) {
                 const int cz = (n3 + zt - 1) / zt;
                 if (zt > 1 && (n3 + cz - 1) / cz != zt) continue;  // same split as a smaller zt
-                const int64_t G = tiles * zt;
-                const int64_t rounds = (G + cus - 1) / cus;
-                const double cost = (double)rounds * (cz + 2 * h) * threads + 1e-2 * halo - 1e-4 * cx;
+                const int64_t G = tiles * zt, slots = (int64_t)cus * per_cu;
+                const int64_t rounds = (G + slots - 1) / slots;
+                const int res = waves * (int)std::min<int64_t>(per_cu, (G + cus - 1) / cus);
+                // wide tiles run into LDS bank conflicts in the x runs (200^3, h = 4: 40 x 12
+                // 86 us per stage, 12 x 40 81 us)
+                const double phase = (0.4 + 0.05 * res * (0.7 + 0.3 / fill)) * (cx > cy + 4 ? 1.06 : 1.0) *
+                                     (res > waves ? 0.9 : 1.0);
+                const double cost = rounds * (3.0 + 2 * h * 0.02 * res + (cz + 3) * phase) + 1e-5 * halo - 1e-6 * cx;
                 if (cost < best) {
                     best = cost;
                     *cx_ = cx, *cy_ = cy, *cz_ = cz;
@@ -333,7 +349,6 @@ nd_kernel_config default_config(const nd_problem* p) {
         else c.tile = p->n <= (int64_t(1) << 20) ? 512 : 1024;
         c.block = ring_block(c.tile);
     } else if (p->topo == ND_CUBE3D) {
-        // e.g. 25 x 20 x 67 on a 200^3 lattice at h = 4: 240 work items, one round
         const int h = (int)p->radius;
         int cx, cy, cz;
         cube_tiles(p, device_cu_count(), &cx, &cy, &cz);
@@ -898,7 +913,7 @@ nd_status enqueue_chunk(const Group& g, int chunk, hipStream_t st) {
         if (!cube_select(g.model, g.prec, g.h, &L))
             return fail(ND_ERR_UNSUPPORTED, "no cube kernel for model %d, h = %d", g.model, g.h);
         const int block = cube_block(g.h, g.tile, g.tile_y);
-        const size_t smem = cube_smem_bytes(g.h, g.tile, g.tile_y, cube_lds_buffers(g.model, g.prec, g.h));
+        const size_t smem = cube_smem_bytes(g.h, g.tile, g.tile_y);
         for (int j = 0; j < chunk; ++j)
             for (int s = 1; s <= 4; ++s)
                 if ((e = cube_launch_stage(L, grid, block, smem, st, g.desc, g.work, g.nwork, s, j, g.mv)) != hipSuccess)

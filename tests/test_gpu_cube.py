@@ -219,3 +219,32 @@ def test_cube_full_200_fp32_bulk_200_steps_against_fp64(nd):
     print(f"cube 200^3 fp32-bulk vs fp64 after 200 steps {e:.3e}")
     assert e < 1e-4
     assert np.max(np.abs(R32 - R64)) < 1e-4
+
+
+@pytest.mark.parametrize("h", [1, 2, 3, 4])
+@pytest.mark.parametrize("tile", [(1, 1, 1), (2, 5, 2), (4, 3, 3), (7, 2, 100), (3, 9, 1)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_cube_tile_edges_against_oracle(nd, h, tile, prec):
+    """Tiles whose extents the run length of three does not divide, work items of
+    fewer planes than the plane loop is deep, and one work item over all planes, on a
+    lattice of different odd extents.  Five steps: FP64 1e-12 (re-associated sums of
+    at most 729 unit terms divided by their number), FP32-bulk 1e-5 (maps and slopes
+    rounded to float, 6e-8, times the steps and the stages)."""
+    n1, n2, n3 = 11, 13, 9
+    prm = [0.2, 1.0, 0.8]
+    y0 = inputs.kuramoto_phases(17 + h, n1 * n2 * n3)
+    print(f"case cube tile edges h={h} tile={tile} prec={prec}", flush=True)
+    p = nd.problem(nd.ND_KURAMOTO, nd.ND_CUBE3D, n1 * n2 * n3, prm, precision=prec, radius=h, dims=(n1, n2, n3))
+    hd = nd.nd_create(p)
+    try:
+        c = nd.nd_get_config(hd)
+        c.tile, c.tile_y, c.tile_z = tile
+        nd.nd_set_config(hd, c)
+        nd.nd_set_state(hd, y0, on_device=0)
+        nd.nd_run(hd, 0.05, 5)
+        y = np.empty_like(y0)
+        nd.nd_get_state(hd, y, on_device=0)
+    finally:
+        nd.nd_destroy(hd)
+    ref, _, _ = O.run(O.cube(n1, h, prm, n2, n3), y0, 0.05, 5)
+    assert np.max(np.abs(y - ref)) / np.max(np.abs(ref)) < (1e-12 if prec == 0 else 1e-5)
