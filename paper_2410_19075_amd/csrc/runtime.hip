@@ -169,31 +169,51 @@ static int ball_runs(int P, int pz) {
     return (c + 7) / 8 * 8;
 }
 
-// Ball tiling and workgroup size.  Halo rows of HX = cx + 2P <= 64 lanes, at
-// most 4 rows per wave and one output per thread, the prefix ring within the
-// LDS budget.  A 256-thread workgroup leaves room for up to 4 per CU (LDS
-// permitting), a 1024-thread one holds the CU alone.  The estimated time is
-// (rounds of workgroups over the CU slots) x (planes per work item incl. the
-// 2P lead-in) x (halo rows per wave + the outputs' prefix reads / 10).
-// Plane-scatter form: 512-thread workgroups, two per CU where the radius is
-// built for it and the two prefix planes fit twice in LDS.  Per plane every wave
-// maps up to 4 halo rows (~720 clocks of issue per row and SIMD), then the
-// outputs read two prefix values per (|dz|, dy) run pair: the larger of the
-// pairs' VALU issue (~48 clocks per pair and SIMD) and their LDS traffic (cx*cy
-// outputs x 32 bytes per pair at 128 bytes per clock).  Work items pay the 2P
-// lead-in planes in mapping only; a CU running two work items at once is
-// counted at 0.8 of running them one after the other (measured at P = 6).
-// The default for radii from kBallScatterMinP (at smaller radii the gather
-// form measured faster).
+// The distinct splits of n3 planes into at most 256 runs: (planes per run, runs).
+static std::vector<std::pair<int, int>> z_splits(int n3) {
+    std::vector<std::pair<int, int>> s;
+    for (int zt = 1; zt <= std::min(n3, 256); ++zt) {
+        const int cz = (n3 + zt - 1) / zt;
+        if ((n3 + cz - 1) / cz == zt) s.emplace_back(cz, zt);
+    }
+    if (s.empty() || s[0].second != 1) s.insert(s.begin(), {n3, 1});
+    return s;
+}
+
+// Plane-scatter form: 512-thread workgroups, two per CU where the radius is built
+// for it and the two prefix planes fit twice in LDS.  The stage time of a tiling is
+// predicted by a sum whose terms are what a work item does and whose weights (us)
+// were fitted to 700 measured stages (radii 1 to 8, lattices of 33 to 100 an edge,
+// both models and precisions; 7 % rms): per plane a constant and the halo rows, as
+// rounds over the waves and as rows; per run pair executed (a pair is skipped where
+// neither of its output planes is the item's) a constant and the output waves; per
+// output plane the output waves.  `resident` work items share a CU and `rounds` of
+// them follow one another.  It replaced a model fitted at P = 6 to the kernel before
+// (us per stage, that one / now, inertia FP64: 100^3 P = 6 82 / 77; 33 x 37 x 41 P = 6
+// 34 / 28, P = 4 24 / 19).  Below radius kBallScatterMinP the gather form is the
+// default; block 512 selects this one there too.
 constexpr int kBallScatterMinP = 3;
 static bool ball_tiles_scatter(const nd_problem* p, int cus, int* cx_, int* cy_, int* cz_) {
     const int P = (int)p->radius;
     if (p->topo != ND_BALL3D || !ball_scatter_available(P) || P < kBallScatterMinP) return false;
     const int n1 = (int)p->n1, n2 = (int)p->n2, n3 = (int)p->n3;
     const int waves = kBallScatterBlock / 64;
-    int pairs = 0;  // runs of dz >= 0 (those of -dz share their reads)
-    for (int dz = 0; dz <= P; ++dz)
-        for (int dy = -P; dy <= P; ++dy) pairs += dz * dz + dy * dy <= P * P;
+    int pairs[kBallMaxP + 1];  // run pairs of |dz| = A
+    for (int A = 0; A <= P; ++A) {
+        pairs[A] = 0;
+        for (int dy = -P; dy <= P; ++dy) pairs[A] += A * A + dy * dy <= P * P;
+    }
+    std::vector<std::pair<int, double>> runs;  // planes per work item, run pairs it executes
+    for (const auto& [cz, zt] : z_splits(n3)) {
+        (void)zt;
+        double e = 0.0;
+        for (int A = 0; A <= P; ++A) {
+            // planes q with an output plane q - P - A or q - P + A in [0, cz)
+            const int hit = A == 0 ? cz : 2 * cz - std::max(0, cz - 2 * A);
+            e += (double)pairs[A] * hit;
+        }
+        runs.emplace_back(cz, e);
+    }
     double best = 1e300;
     bool found = false;
     for (int cx = 1; cx <= std::min(n1, 64 - 2 * P); ++cx) {
@@ -202,16 +222,17 @@ static bool ball_tiles_scatter(const nd_problem* p, int cus, int* cx_, int* cy_,
             const size_t sm = ball_scatter_smem_bytes(P, cx, cy);
             if (sm > kBallSmemMax) break;
             const int per_cu = P <= kBallScatterPairedMaxP && 2 * sm <= kBallSmemMax ? 2 : 1;
-            const double overlap = per_cu == 2 ? 0.8 : 1.0;
             const int64_t tiles = (int64_t)((n1 + cx - 1) / cx) * ((n2 + cy - 1) / cy);
-            const double map = 720.0 * ((cy + 2 * P + waves - 1) / waves);
-            const double sums = std::max(48.0 * pairs, (double)cx * cy * pairs * 32.0 / 128.0);
-            for (int zt = 1; zt <= std::min(n3, 256); ++zt) {
-                const int cz = (n3 + zt - 1) / zt;
-                if (zt > 1 && (n3 + cz - 1) / cz != zt) continue;
-                const int64_t rounds = (tiles * zt + (int64_t)cus * per_cu - 1) / ((int64_t)cus * per_cu);
-                const double cost =
-                    (double)rounds * per_cu * overlap * ((cz + 2 * P) * map + cz * sums) - 1e-6 * cx * cy;
+            const double rows = (double)(cy + 2 * P) / waves, row_rounds = std::ceil(rows);
+            const int out_waves = (cx * cy + 63) / 64;
+            for (const auto& [cz, e] : runs) {
+                const int64_t G = tiles * ((n3 + cz - 1) / cz);
+                const int64_t rounds = (G + (int64_t)cus * per_cu - 1) / ((int64_t)cus * per_cu);
+                const int resident = (int)std::min<int64_t>(per_cu, (G + cus - 1) / cus);
+                const int planes = cz + 2 * P;
+                const double item = planes * (0.349 + resident * (0.149 * row_rounds + 0.166 * rows)) +
+                                    e * (0.0325 + 0.0021 * resident * out_waves) + 0.056 * cz * resident * out_waves;
+                const double cost = 5.2 + rounds * item - 1e-6 * cx * cy;
                 if (cost < best) {
                     best = cost;
                     found = true;
@@ -223,13 +244,29 @@ static bool ball_tiles_scatter(const nd_problem* p, int cus, int* cx_, int* cy_,
     return found;
 }
 
-static void ball_tiles_gather(const nd_problem* p, int cus, int* cx_, int* cy_, int* cz_, int* bs_) {
+// Gather form (disks, and balls below radius kBallScatterMinP).  Halo rows of HX =
+// cx + 2P <= 64 lanes, at most 4 rows per wave and one output per thread, the prefix
+// ring within the LDS budget.  A 256-thread workgroup leaves room for up to 4 per CU
+// (LDS permitting), a 1024-thread one holds the CU alone.  The estimated time is
+// (rounds of workgroups over the CU slots) x (planes per work item incl. the 2P
+// lead-in) x (halo rows per wave + the outputs' prefix reads / 10).
+// With `fitted` the tile for the workgroup size *bs_ is chosen by a predicted stage
+// time (us) fitted to 860 measured stages of radius 1 and 2 (lattices of 30 to 120 an
+// edge, 9 % rms): per plane a constant and the halo rows, per output plane a
+// constant and the output waves' runs.  The estimate's tile / this one's, us per
+// stage, inertia FP64: 100^3 P = 1 27 / 24, 60 x 50 x 40 P = 1 10.9 / 9.2, 33 x 37 x 41
+// P = 2 12.1 / 10.4.
+static void ball_tiles_gather(const nd_problem* p, int cus, bool fitted, int* cx_, int* cy_, int* cz_, int* bs_) {
     const int P = (int)p->radius, pz = ball_pz(p->topo, p->radius);
     const int n1 = (int)p->n1, n2 = (int)p->n2, n3 = (int)p->n3;
-    const double reads = 0.1 * ball_runs(P, pz);
+    const double runs = ball_runs(P, pz), reads = 0.1 * runs;
+    const auto splits = z_splits(n3);
     double best = 1e300;
-    *cx_ = 1, *cy_ = 1, *cz_ = n3, *bs_ = 1024;
+    *cx_ = 1, *cy_ = 1, *cz_ = n3;
+    if (!fitted) *bs_ = 1024;
+    const int only = fitted ? *bs_ : 0;
     for (int bs : {256, 1024}) {
+        if (only && bs != only) continue;
         const int waves = bs / 64;
         for (int cx = 1; cx <= std::min(n1, 64 - 2 * P); ++cx) {
             for (int cy = 1; cy <= std::min(n2, 4 * waves - 2 * P); ++cy) {
@@ -239,11 +276,18 @@ static void ball_tiles_gather(const nd_problem* p, int cus, int* cx_, int* cy_, 
                 const int per_cu = bs == 1024 ? 1 : std::max(1, std::min<int>(4, (int)(kBallSmemMax / sm)));
                 const int64_t tiles = (int64_t)((n1 + cx - 1) / cx) * ((n2 + cy - 1) / cy);
                 const double plane_cost = (double)((cy + 2 * P + waves - 1) / waves) + reads;
-                for (int zt = 1; zt <= std::min(n3, 256); ++zt) {
-                    const int cz = (n3 + zt - 1) / zt;
-                    if (zt > 1 && (n3 + cz - 1) / cz != zt) continue;
+                for (const auto& [cz, zt] : splits) {
                     const int64_t rounds = (tiles * zt + (int64_t)cus * per_cu - 1) / ((int64_t)cus * per_cu);
-                    const double cost = (double)rounds * (cz + 2 * pz) * plane_cost - 1e-6 * cx * cy;
+                    double cost = (double)rounds * (cz + 2 * pz) * plane_cost - 1e-6 * cx * cy;
+                    if (fitted) {
+                        const int resident = (int)std::min<int64_t>(per_cu, (tiles * zt + cus - 1) / cus);
+                        const double share = resident * waves / 16.0, rows = (double)(cy + 2 * P) / waves;
+                        const double outs = (cx * cy + 63) / 64 * resident / 16.0;
+                        cost = 5.7 +
+                               rounds * ((cz + 2 * pz) * (0.208 + share * (0.263 * std::ceil(rows) + 0.436 * rows)) +
+                                         cz * (0.8 + outs * (0.668 + 0.0629 * runs))) -
+                               1e-6 * cx * cy;
+                    }
                     if (cost < best) {
                         best = cost;
                         *cx_ = cx, *cy_ = cy, *cz_ = cz, *bs_ = bs;
@@ -259,13 +303,14 @@ static void ball_tiles(const nd_problem* p, int cus, int* cx_, int* cy_, int* cz
         *bs_ = kBallScatterBlock;
         return;
     }
-    ball_tiles_gather(p, cus, cx_, cy_, cz_, bs_);
+    ball_tiles_gather(p, cus, false, cx_, cy_, cz_, bs_);
+    if (p->topo == ND_BALL3D) ball_tiles_gather(p, cus, true, cx_, cy_, cz_, bs_);
 }
 
 nd_kernel_config ball_gather_config(const nd_problem* p) {
     nd_kernel_config c = default_config(p);
     int cx, cy, cz, bs;
-    ball_tiles_gather(p, device_cu_count(), &cx, &cy, &cz, &bs);
+    ball_tiles_gather(p, device_cu_count(), false, &cx, &cy, &cz, &bs);
     c.tile = cx;
     c.tile_y = cy;
     c.tile_z = cz;
@@ -304,6 +349,7 @@ static void cube_tiles(const nd_problem* p, int cus, int* cx_, int* cy_, int* cz
     const int h = (int)p->radius;
     const int n1 = (int)p->n1, n2 = (int)p->n2, n3 = (int)p->n3;
     const int run = cube_run(h);
+    const auto splits = z_splits(n3);
     double best = 1e300;
     *cx_ = 1, *cy_ = 1, *cz_ = n3;
     for (int cx = 1; cx <= std::min(n1, 64); ++cx) {
@@ -316,9 +362,7 @@ static void cube_tiles(const nd_problem* p, int cus, int* cx_, int* cy_, int* cz
             const int64_t tiles = (int64_t)((n1 + cx - 1) / cx) * ((n2 + cy - 1) / cy);
             // share of the run threads' work that is kept
             const double fill = (double)cx * cy / (((cx + run - 1) / run * run) * (double)((cy + run - 1) / run * run));
-            for (int zt = 1; zt <= std::min(n3, 256); ++zt) {
-                const int cz = (n3 + zt - 1) / zt;
-                if (zt > 1 && (n3 + cz - 1) / cz != zt) continue;  // same split as a smaller zt
+            for (const auto& [cz, zt] : splits) {
                 const int64_t G = tiles * zt, slots = (int64_t)cus * per_cu;
                 const int64_t rounds = (G + slots - 1) / slots;
                 const int res = waves * (int)std::min<int64_t>(per_cu, (G + cus - 1) / cus);
