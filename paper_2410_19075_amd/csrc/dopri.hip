@@ -58,71 +58,99 @@ struct DenseOut {
     int64_t y_stride;
 };
 
+// Bound: FP64 issue, 7 stages of the resident RK4 kernel's work and 34 coefficient
+// FMAs per element and accepted step.  Measured per attempt (rings of 1024, one /
+// 512): Kuramoto 8.3 / 19 us, FHN 6.9 / 14.6 us; with four barriers per stage, the
+// prefix completed in LDS and branches on the wrap 14.1 / 25.6 and 12.9 / 26.7 us.
 template <int MODEL, bool DENSE>
 __device__ __forceinline__ void ring_dopri(const NetDesc* __restrict__ D, const double* __restrict__ t_end,
                                            double rtol, double atol, int64_t max_steps, double* __restrict__ stats,
                                            DenseOut out) {
     using M = RingModel<MODEL, double>;
-    constexpr int V = M::V, T = kDpCap, EPT = kDpEPT, NW = kDpBS / kWave;
-    __shared__ double pf[2 * T];  // inclusive prefix sums of the two map components
-    __shared__ double lds[8 * NW];
-    const int tid = threadIdx.x;
+    constexpr int V = M::V, EPT = kDpEPT, NW = kDpBS / kWave;
+    // prefix k (sum of the maps before element k), k = 0 .. capacity, at k + k / EPT
+    auto px = [](int k) { return (k + k / EPT) * (int)sizeof(double2); };
+    __shared__ __align__(16) char pf[(kDpCap + kDpBS + 1) * sizeof(double2)];
+    auto pre = [&](int off) -> double2& { return *(double2*)(pf + off); };
+    __shared__ double2 wtot[NW];
+    __shared__ double lds[2 * NW];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
     const NetDesc& d = D[blockIdx.x];
     const int n = (int)d.n, P = (int)d.P;
+    const ModelConst mc(d);
+    const bool act = wid * kWave * EPT < n;  // waves without elements only join the barriers
     ND_GLOBAL double* y_g = gp(d.y[d.ypar]);
     double y[EPT][V], k[7][EPT][V];
+    // window [i-P, i+P] = prefix(hi) - prefix(lo), plus the ring total where it wraps
+    int hi[EPT], lo[EPT];
+    bool wrap[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        const int i = tid * EPT + e;
+        int h = i + P + 1, l = i - P;
+        wrap[e] = l < 0 || h > n;
+        if (l < 0) l += n;
+        if (h > n) h -= n;
+        hi[e] = px(i < n ? h : 0);
+        lo[e] = px(i < n ? l : 0);
+    }
+    if (tid == 0) pre(0) = make_double2(0.0, 0.0);
+    if (!act && lane == 0) wtot[wid] = make_double2(0.0, 0.0);
+    const int rtot = px(n);
 #pragma unroll
     for (int e = 0; e < EPT; ++e) {
         const int i = tid * EPT + e;
 #pragma unroll
         for (int v = 0; v < V; ++v) y[e][v] = i < n ? y_g[(int64_t)v * n + i] : 0.0;
     }
-    // slopes of stage value z: map, block prefix sums, window sums, RHS
+    // slopes of stage value z: map, block prefix sums, window sums, RHS.  Two barriers
+    // and one LDS write per element, as in the resident RK4 kernel: the next stage's
+    // wave totals are written after this stage's second barrier, its prefixes after
+    // the first barrier that follows this stage's reads.  (Elements past n compute
+    // slopes nobody reads.)
     auto slopes = [&](const double (&z)[EPT][V], double (&kout)[EPT][V]) {
-        double2 x[EPT];
-        double tot[2] = {0.0, 0.0};
+        double2 x[EPT], in[EPT];
+        double2 ex = make_double2(0.0, 0.0);
+        if (act) {
+            double2 tot = make_double2(0.0, 0.0);
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int i = tid * EPT + e;
-            x[e] = M::map(z[e]);
-            if (i >= n) x[e] = make_double2(0.0, 0.0);
-            tot[0] += x[e].x;
-            tot[1] += x[e].y;
-            pf[tid * EPT + e] = tot[0];
-            pf[T + tid * EPT + e] = tot[1];
-        }
-        block_exscan<kDpBS, 2>(tot, lds);
-#pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            pf[tid * EPT + e] += tot[0];
-            pf[T + tid * EPT + e] += tot[1];
+            for (int e = 0; e < EPT; ++e) {
+                x[e] = M::map(z[e]);
+                if (tid * EPT + e >= n) x[e] = make_double2(0.0, 0.0);
+                tot.x += x[e].x;
+                tot.y += x[e].y;
+                in[e] = tot;
+            }
+            const double2 incl = make_double2(wave_incl_scan(tot.x), wave_incl_scan(tot.y));
+            if (lane == kWave - 1) wtot[wid] = incl;
+            ex = make_double2(wave_shift_up1(incl.x), wave_shift_up1(incl.y));
         }
         lds_barrier();
-        const double t0 = pf[n - 1], t1 = pf[T + n - 1];
+        if (act) {
+            const double2 before = waves_before<NW>(wtot, wid);
+            ex.x += before.x;
+            ex.y += before.y;
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int i = tid * EPT + e;
+            for (int e = 0; e < EPT; ++e)
+                pre(px(tid * EPT + e + 1)) = make_double2(ex.x + in[e].x, ex.y + in[e].y);
+        }
+        lds_barrier();
+        if (act) {
+            const double2 T = pre(rtot);
+            double2 ph[EPT], pl[EPT];
 #pragma unroll
-            for (int v = 0; v < V; ++v) kout[e][v] = 0.0;
-            if (i < n) {
-                const int lo = i - P, hi = i + P + 1;
-                auto pre = [&](int q, int c) { return q == 0 ? 0.0 : pf[c * T + q - 1]; };
-                double w0, w1;
-                if (lo < 0) {
-                    w0 = pre(hi, 0) + (t0 - pre(lo + n, 0));
-                    w1 = pre(hi, 1) + (t1 - pre(lo + n, 1));
-                } else if (hi > n) {
-                    w0 = (t0 - pre(lo, 0)) + pre(hi - n, 0);
-                    w1 = (t1 - pre(lo, 1)) + pre(hi - n, 1);
-                } else {
-                    w0 = pre(hi, 0) - pre(lo, 0);
-                    w1 = pre(hi, 1) - pre(lo, 1);
-                }
-                const double2 W = make_double2(w0 - x[e].x, w1 - x[e].y);
-                M::rhs(d, z[e], x[e], W, kout[e]);
+            for (int e = 0; e < EPT; ++e) {
+                ph[e] = pre(hi[e]);
+                pl[e] = pre(lo[e]);
+            }
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) {
+                const double2 t = wrap[e] ? T : make_double2(0.0, 0.0);
+                const double2 W = make_double2(ph[e].x + (t.x - pl[e].x) - x[e].x, ph[e].y + (t.y - pl[e].y) - x[e].y);
+                M::rhs(mc, z[e], x[e], W, kout[e]);
             }
         }
-        lds_barrier();  // pf is rewritten by the next stage
     };
     // dense output k: the state y + hs sum_q w_q(theta) k_q (theta = 0: y itself), its
     // order parameter by a fixed-order block reduction
@@ -188,8 +216,8 @@ __device__ __forceinline__ void ring_dopri(const NetDesc* __restrict__ D, const 
                 for (int v = 0; v < V; ++v) {
                     double a = 0.0;
 #pragma unroll
-                    for (int q = 0; q < s; ++q) a += kDpA[s][q] * k[q][e][v];
-                    z[e][v] = y[e][v] + hs * a;
+                    for (int q = 0; q < s; ++q) a = fma(kDpA[s][q], k[q][e][v], a);
+                    z[e][v] = fma(hs, a, y[e][v]);
                 }
             slopes(z, k[s]);
         }
@@ -205,9 +233,9 @@ __device__ __forceinline__ void ring_dopri(const NetDesc* __restrict__ D, const 
                 for (int v = 0; v < V; ++v) {
                     double er = 0.0;
 #pragma unroll
-                    for (int q = 0; q < 7; ++q) er += kDpE[q] * k[q][e][v];
+                    for (int q = 0; q < 7; ++q) er = fma(kDpE[q], k[q][e][v], er);
                     er *= hs;
-                    const double sc = atol + rtol * fmax(fabs(y[e][v]), fabs(z[e][v]));
+                    const double sc = fma(rtol, fmax(fabs(y[e][v]), fabs(z[e][v])), atol);
                     sum[0] += (er / sc) * (er / sc);
                 }
             }

@@ -154,7 +154,10 @@ struct RingModel<ND_KURAMOTO_INERTIA, KT> {
 template <class KT>
 struct RingModel<ND_FHN, KT> {
     static constexpr int V = 2;
-    __device__ static __forceinline__ double2 map(const double* z) { return make_double2(z[0], z[1]); }
+    template <bool SC = false>
+    __device__ static __forceinline__ double2 map(const double* z) {
+        return make_double2(z[0], z[1]);
+    }
     template <class D>
     __device__ static __forceinline__ void rhs(const D& d, const double* z, double2 xo, double2 W, double* k) {
         (void)xo;

@@ -347,3 +347,18 @@ def test_adaptive_on_compressed_coupling_matrices(nd, model, kind, t_end, rtol):
     print(f"  gpu {st.accepted}/{st.rejected}  oracle {acc}/{rej}", flush=True)
     assert (st.accepted, st.rejected) == (acc, rej) and st.t == t
     assert normwise(y, ref, nv) < 1e-10
+
+
+@pytest.mark.parametrize("n,P", [(3, 1), (64, 31), (127, 63), (128, 1), (129, 64), (1023, 511), (1024, 2)])
+@pytest.mark.parametrize("model", ["kuramoto", "fhn", "inertia"])
+def test_adaptive_ring_at_wave_and_capacity_edges(nd, model, n, P):
+    """Rings of one workgroup whose last wave is full, ragged or alone, with windows
+    that wrap for every element: the oracle's steps, and its state to 1e-10 (the step
+    sizes agree to the rounding of err^(-1/5), a relative 1e-8 of an error estimate of
+    1e-8, so the trajectories differ by far less than the tolerance 1e-8)."""
+    print(f"case adaptive edges {model} n={n} P={P}", flush=True)
+    p, onet, y0, nv = net(nd, model, n, P, n + P)
+    (y,), (st,) = run_gpu(nd, [p], [y0], [1.0], [1e-3], 1e-8, 1e-10)
+    ref, t, acc, rej, hnext = O.run_dopri(onet, y0, 1.0, 1e-8, 1e-10, 1e-3)
+    assert (st.accepted, st.rejected) == (acc, rej)
+    assert normwise(y, ref, nv) < 1e-10
