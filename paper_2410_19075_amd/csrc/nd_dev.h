@@ -72,8 +72,9 @@ struct NetDesc {
     int64_t g0;         // run step index at the start of the current chunk
     int64_t nsteps;     // steps still to do at the start of the current chunk
     int32_t ypar;       // which y buffer holds the state at the start of the chunk
+    int32_t fresh;      // a new state was set: the run starts by clearing the status word
     int32_t* status;    // the network's status word: stage 4 stores 1 there when it produces a
-                        // non-finite state value (cleared when a new state is set)
+                        // non-finite state value (cleared by the first run after a new state)
 };
 
 

@@ -48,6 +48,10 @@ struct Net {
     double* mv_dev = nullptr;
     NetDesc* solo_desc = nullptr;  // descriptor for running this network alone
     int32_t* status_dev = nullptr;   // status word the stage kernels flag (non-finite state)
+    // a new state was set and no run has started since: the device's status word is
+    // out of date (read as clear) and the next run clears it with its descriptors, so
+    // setting a state launches nothing besides the copy
+    bool status_stale = false;
     int32_t* status_host = nullptr;  // pinned copy, read after a synchronising call
     hipEvent_t last_ev = nullptr;    // recorded after the last work enqueued for this network alone
     std::shared_ptr<RunEvent> batch_ev;  // else the event of the batch that last ran it
@@ -109,8 +113,6 @@ nd_status enqueue_chunk(const Group& g, int chunk, hipStream_t st);
 // Write one descriptor into device memory in stream order (the value travels as a
 // kernel argument, so no host buffer has to outlive the call).
 hipError_t put_desc(NetDesc* dst, const NetDesc& d, hipStream_t st);
-// Clear a network's status word in stream order.
-hipError_t clear_status(int32_t* status, hipStream_t st);
 nd_status capture_chunk(const Group& g, int K, hipGraphExec_t* out);
 bool graphs_enabled();
 nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t* steps, const nd_observe* obs,

@@ -171,6 +171,54 @@ def test_nonfinite_state_is_reported_for_that_network_only(nd, kind):
     assert np.array_equal(ya, ys)
 
 
+@pytest.mark.parametrize("kind", ["ring_resident", "cube", "csr"])
+@pytest.mark.parametrize("batch", [False, True])
+def test_new_state_resets_only_its_own_status(nd, kind, batch):
+    """The status word belongs to the state: of two failed networks, the one that
+    is set anew runs clean (alone and in a batch with the other), the other one
+    keeps its failure."""
+    import torch
+    p, y0, dt = _cases(nd)[kind]
+    bad = y0.copy()
+    bad[len(bad) // 3] = np.nan
+    good, bad = torch.from_numpy(y0).cuda(), torch.from_numpy(bad).cuda()
+    ha, hb = nd.nd_create(p), nd.nd_create(p)
+    hs = [ha, hb]
+
+    def run():
+        if batch:
+            nd.nd_run_batch(hs, [dt, dt], [5, 5])
+        else:
+            for h in hs:
+                nd.nd_run(h, dt, 5)
+
+    def fails(h):
+        with pytest.raises(nd.NDError) as ei:
+            nd.nd_sync(h)
+        assert ei.value.status == nd.ND_ERR_NUMERIC
+
+    try:
+        for h in hs:
+            nd.nd_set_state(h, bad)
+        run()
+        fails(ha)
+        fails(hb)
+        nd.nd_set_state(ha, good)
+        nd.nd_sync(ha)
+        fails(hb)
+        run()
+        nd.nd_sync(ha)
+        fails(hb)
+        run()
+        nd.nd_sync(ha)
+        nd.nd_set_state(ha, bad)
+        run()
+        fails(ha)
+    finally:
+        nd.nd_destroy(ha)
+        nd.nd_destroy(hb)
+
+
 def test_server_fails_a_diverging_request_alone(nd):
     """An FHN request with a step far beyond the model's stability limit blows up
     within a few steps; the server fails it at the next chunk boundary with
