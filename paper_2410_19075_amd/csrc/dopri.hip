@@ -310,16 +310,32 @@ __global__ __launch_bounds__(kDpBS) __attribute__((amdgpu_waves_per_eu(4))) void
 
 
 // ------------------------------------------------------------ tiled rings
-// Rings larger than one workgroup: the same method and step control, with
-// every stage spread over tiles of 512 elements in three launches (stage value,
-// its map and the tile's prefix sums; the tiles' offsets; window sums, RHS and,
-// at the last stage, the error terms), and one controller launch per step
-// attempt that takes the accept / reject decision on the device.  The host
-// replays attempts in groups and only reads back whether every ring is done.
+// Rings larger than one workgroup and compressed coupling matrices: the same method
+// and step control over tiles, one launch per stage.  The launch of stage s takes
+// the neighbour sums of the stage value z_s from what the launch before it left
+// (rings: global prefix sums of the map; matrices: the maps), evaluates the slope
+// and, since z_{s+1} needs no slope of another element, goes on to z_{s+1}, its map
+// and the tile's prefix sums, double-buffered.  An attempt is the launch that forms
+// z_1 (it depends on the controller's step), six stage launches and one controller
+// launch that takes the accept / reject decision on the device.  The host replays
+// attempts in groups and only reads back whether every network is done.
 // Window sums come from global prefix sums of the map: the prefix of element k
-// is its tile's offset (fixed-order scan of the tile totals) plus its
-// in-tile inclusive prefix.
-constexpr int kDtBS = 256, kDtEPT = 2, kDtT = kDtBS * kDtEPT;
+// is its tile's offset (fixed-order scan of the tile totals) plus its in-tile
+// inclusive prefix.
+// Bound: launches and their latency up to some 10^5 elements, HBM beyond, the rows'
+// gathers for matrices.  Per attempt, against a map launch and an RHS launch per
+// stage: FHN ring of 65,536 90 -> 69 us, of 10^6 361 -> 307 us, four Kuramoto rings of
+// 65,536 132 -> 107 us; 60^3 inertia matrix network (65 links a row) with its outputs
+// 4.22 -> 2.74 ms a run to t = 50, its tiles of 512 -> 256 and the outputs' slopes read
+// once included.
+constexpr int kDtBS = 256;
+// Elements per thread and tile: matrices take one, which gives twice the workgroups
+// to hide the gathers (and needs no prefix); rings two, which halves the tile totals
+// every workgroup scans.
+template <int TOPO>
+struct DtTile {
+    static constexpr int EPT = TOPO == ND_LINKS ? 1 : 2, T = kDtBS * EPT;
+};
 // rings of at most this many tiles get their tile offsets in each RHS workgroup
 // (a scan of the tile totals into LDS); longer rings in a launch of their own
 constexpr int kDtScanMax = 2048;
@@ -340,14 +356,14 @@ struct DtCtl {
 // Per-ring buffers of one call.
 struct DtNet {
     int32_t n, P, G, V;
-    int32_t gather;   // the RHS reads other elements' maps (compressed coupling matrix)
     double tend;
     double* y[2];     // state, and the fifth-order solution of the attempt
     double* k[7];     // stage slopes (physical buffers)
     double* Z;        // stage value of stages 1 .. 5 (stage 0 is y, stage 6 goes to y[ypar ^ 1])
-    double* M;        // [n] map of the current stage value, as double2 (written when gather is set)
-    double* pre;      // [2][n] in-tile inclusive prefix of M
-    double* tot;      // [2][G] tile totals, then (after the offsets launch) exclusive offsets
+    // of the stage value of stage s, in buffer s & 1:
+    double* M[2];     // matrices: [n] its map, as double2
+    double* pre[2];   // rings: [2][n] in-tile inclusive prefix of its map
+    double* tot[2];   // rings: [2][G] tile totals, then (after the offsets launch) exclusive offsets
     double* errp;     // [G] error partial sums of the attempt
     DtCtl* ctl;
     int64_t K;        // dense output: last output index (-1: none)
@@ -356,83 +372,93 @@ struct DtNet {
     double* Y;        // dense output: states at the outputs (device, may be NULL)
 };
 
-// Stage value z of stage S (S = 0: the state; S = 6: the fifth-order
-// solution, kept in y[ypar ^ 1]), its map and the tile's inclusive prefix.
-// Element e * kDtBS + tid of the tile belongs to thread tid, so every access
-// of a wave is one contiguous run; the stage is a template parameter so the
-// slopes' loads are all issued before the sums that use them.
-template <int MODEL, int S>
-__global__ __launch_bounds__(kDtBS) void k_dt_map(const DtNet* __restrict__ R, const int2* __restrict__ work) {
+// What a launch leaves for the stage that follows: the maps (matrices) or the tile's
+// inclusive prefix sums and totals (rings) of the tile's stage values, in buffer b.
+// Element e * kDtBS + tid of the tile belongs to thread tid, so every access of a
+// wave is one contiguous run.  lds: 4 * EPT * (kDtBS / 64) doubles.
+template <int TOPO>
+__device__ __forceinline__ void dt_leave(const DtNet& r, int b, int tile, const double2 (&x)[DtTile<TOPO>::EPT],
+                                         double* lds) {
+    constexpr int EPT = DtTile<TOPO>::EPT, T = DtTile<TOPO>::T, NE = 2 * EPT;
+    const int n = r.n, i0 = tile * T + (int)threadIdx.x;
+    if constexpr (TOPO == ND_LINKS) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e)
+            if (i0 + e * kDtBS < n) ((double2*)r.M[b])[i0 + e * kDtBS] = x[e];
+    } else {
+        // block sums and thread-exclusive prefixes of each element run
+        double bs[NE], ex[NE];
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            bs[2 * e] = ex[2 * e] = x[e].x;
+            bs[2 * e + 1] = ex[2 * e + 1] = x[e].y;
+        }
+        block_sum_and_exscan<kDtBS, NE, NE>(bs, ex, lds);
+        double off0 = 0.0, off1 = 0.0;
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int i = i0 + e * kDtBS;
+            if (i < n) {
+                r.pre[b][i] = off0 + (ex[2 * e] + x[e].x);
+                r.pre[b][n + i] = off1 + (ex[2 * e + 1] + x[e].y);
+            }
+            off0 += bs[2 * e];
+            off1 += bs[2 * e + 1];
+        }
+        if (threadIdx.x == 0) {
+            r.tot[b][tile] = off0;
+            r.tot[b][r.G + tile] = off1;
+        }
+    }
+}
+
+// The stage value of stage S = 0 (the state, before the first slope) or 1 (z_1 = y +
+// h a_10 k_1 of an attempt) and what the stage launch needs of it.
+template <int MODEL, int TOPO, int S>
+__global__ __launch_bounds__(kDtBS) void k_dt_begin(const DtNet* __restrict__ R, const int2* __restrict__ work,
+                                                    int nwork) {
     using M = RingModel<MODEL, double>;
-    constexpr int V = M::V, NW = kDtBS / kWave, NE = 2 * kDtEPT;
-    __shared__ double lds[2 * NE * NW];
-    const int2 wk = work[blockIdx.x];
+    constexpr int V = M::V, EPT = DtTile<TOPO>::EPT, T = DtTile<TOPO>::T;
+    __shared__ double lds[4 * EPT * (kDtBS / kWave)];
+    const int w = xcd_work(blockIdx.x, nwork);
+    if (w < 0) return;
+    const int2 wk = work[w];
     const DtNet& r = R[wk.x];
     const DtCtl c = *r.ctl;
     if (c.done) return;
-    const int n = r.n, t0 = wk.y * kDtT, tid = threadIdx.x;
+    const int n = r.n;
     const double* __restrict__ y = r.y[c.ypar];
-    const double* kq[S > 0 ? S : 1];
+    const double* __restrict__ k0 = r.k[c.f % 7];
+    double2 x[EPT];
 #pragma unroll
-    for (int q = 0; q < S; ++q) kq[q] = r.k[(c.f + q) % 7];
-    double* __restrict__ zo = S == 6 ? r.y[c.ypar ^ 1] : r.Z;
-    double xs[NE];
-#pragma unroll
-    for (int e = 0; e < kDtEPT; ++e) {
-        const int i = t0 + e * kDtBS + tid;
-        double2 x = make_double2(0.0, 0.0);
+    for (int e = 0; e < EPT; ++e) {
+        const int i = wk.y * T + e * kDtBS + (int)threadIdx.x;
+        x[e] = make_double2(0.0, 0.0);
         if (i < n) {
             double z[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) {
                 const int64_t o = (int64_t)v * n + i;
-                double a = 0.0;
-#pragma unroll
-                for (int q = 0; q < S; ++q) a += kDpA[S][q] * kq[q][o];
-                z[v] = S == 0 ? y[o] : y[o] + c.hs * a;
+                z[v] = S == 0 ? y[o] : fma(c.hs, kDpA[1][0] * k0[o], y[o]);
+                if (S > 0) r.Z[o] = z[v];
             }
-            x = M::map(z);
-            if (S > 0) {  // kept for the RHS launch of this stage
-#pragma unroll
-                for (int v = 0; v < V; ++v) zo[(int64_t)v * n + i] = z[v];
-            }
-            if (r.gather) ((double2*)r.M)[i] = x;
+            x[e] = M::map(z);
         }
-        xs[2 * e] = x.x;
-        xs[2 * e + 1] = x.y;
     }
-    // block sums and thread-exclusive prefixes of each element run
-    double bs[NE], ex[NE];
-#pragma unroll
-    for (int q = 0; q < NE; ++q) bs[q] = ex[q] = xs[q];
-    block_sum_and_exscan<kDtBS, NE, NE>(bs, ex, lds);
-    double off0 = 0.0, off1 = 0.0;
-#pragma unroll
-    for (int e = 0; e < kDtEPT; ++e) {
-        const int i = t0 + e * kDtBS + tid;
-        if (i < n) {
-            r.pre[i] = off0 + (ex[2 * e] + xs[2 * e]);
-            r.pre[n + i] = off1 + (ex[2 * e + 1] + xs[2 * e + 1]);
-        }
-        off0 += bs[2 * e];
-        off1 += bs[2 * e + 1];
-    }
-    if (tid == 0) {
-        r.tot[wk.y] = off0;
-        r.tot[r.G + wk.y] = off1;
-    }
+    dt_leave<TOPO>(r, S & 1, wk.y, x, lds);
 }
 
-// Exclusive offsets of the tiles (one workgroup per ring, fixed order).
-__global__ __launch_bounds__(kDtBS) void k_dt_offsets(const DtNet* __restrict__ R) {
+// Exclusive offsets of the tiles of buffer b (one workgroup per ring, fixed order).
+__global__ __launch_bounds__(kDtBS) void k_dt_offsets(const DtNet* __restrict__ R, int b) {
     const DtNet& r = R[blockIdx.x];
     if (r.ctl->done || r.G <= kDtScanMax) return;
     __shared__ double lds[4 * (kDtBS / kWave)];
     __shared__ double chunk[2];
+    double* tot = r.tot[b];
     double carry0 = 0.0, carry1 = 0.0;
     for (int b0 = 0; b0 < r.G; b0 += kDtBS) {
         const int q = b0 + (int)threadIdx.x;
-        const double own0 = q < r.G ? r.tot[q] : 0.0, own1 = q < r.G ? r.tot[r.G + q] : 0.0;
+        const double own0 = q < r.G ? tot[q] : 0.0, own1 = q < r.G ? tot[r.G + q] : 0.0;
         double v[2] = {own0, own1};
         block_exscan<kDtBS, 2>(v, lds);  // v: exclusive prefix in this chunk
         if (threadIdx.x == kDtBS - 1) {
@@ -440,8 +466,8 @@ __global__ __launch_bounds__(kDtBS) void k_dt_offsets(const DtNet* __restrict__ 
             chunk[1] = v[1] + own1;
         }
         if (q < r.G) {
-            r.tot[q] = carry0 + v[0];
-            r.tot[r.G + q] = carry1 + v[1];
+            tot[q] = carry0 + v[0];
+            tot[r.G + q] = carry1 + v[1];
         }
         __syncthreads();
         carry0 += chunk[0];
@@ -450,17 +476,21 @@ __global__ __launch_bounds__(kDtBS) void k_dt_offsets(const DtNet* __restrict__ 
     }
 }
 
-// Neighbour sums (ring: windows from the global prefix; links: the compressed
-// coupling matrix's rows, extracted as in the stage kernels of that topology),
-// the RHS of stage s into k_{s+1} and, at the last stage, the error terms of
-// the attempt.
-template <int MODEL, int TOPO>
-__global__ __launch_bounds__(kDtBS) void k_dt_rhs(const DtNet* __restrict__ R, const NetDesc* __restrict__ D,
-                                                  const int2* __restrict__ work, int nwork, int s, double rtol,
-                                                  double atol) {
+// Stage S of an attempt (0: the first slope of the run): neighbour sums of z_S
+// (ring: windows from the global prefix; links: the compressed coupling matrix's
+// rows, extracted as in the stage kernels of that topology), the RHS into k_{S+1},
+// then for S = 1 .. 5 z_{S+1} (the fifth-order solution, S = 5, into y[ypar ^ 1]) and
+// what its stage needs, for S = 6 the error terms of the attempt.  The stage is a
+// template parameter so the slopes' loads are all issued before the sums that use
+// them.
+template <int MODEL, int TOPO, int S>
+__global__ __launch_bounds__(kDtBS) void k_dt_stage(const DtNet* __restrict__ R, const NetDesc* __restrict__ D,
+                                                    const int2* __restrict__ work, int nwork, double rtol,
+                                                    double atol) {
     using M = RingModel<MODEL, double>;
-    constexpr int V = M::V, NW = kDtBS / kWave;
-    __shared__ double lds[3 * NW];
+    constexpr int V = M::V, EPT = DtTile<TOPO>::EPT, T = DtTile<TOPO>::T, b = S & 1;
+    constexpr bool kNext = S >= 1 && S <= 5;
+    __shared__ double lds[4 * EPT * (kDtBS / kWave)];
     extern __shared__ double dt_off[];  // [2][G]: exclusive tile offsets (rings of <= kDtScanMax tiles)
     // row tiles that share gathers stay on one XCD (its own L2)
     const int w = xcd_work(blockIdx.x, nwork);
@@ -470,64 +500,88 @@ __global__ __launch_bounds__(kDtBS) void k_dt_rhs(const DtNet* __restrict__ R, c
     const NetDesc& d = D[wk.x];
     const DtCtl c = *r.ctl;
     if (c.done) return;
-    const int n = r.n, P = r.P, t0 = wk.y * kDtT, tid = threadIdx.x;
+    const int n = r.n, P = r.P, t0 = wk.y * T, tid = threadIdx.x;
     const int G = r.G;
     const bool local = TOPO == ND_RING && G <= kDtScanMax;  // uniform over the block
+    const double* __restrict__ tot = r.tot[b];
+    const double* __restrict__ pre = r.pre[b];
     if (local) {
         // each thread adds a run of consecutive tile totals; the block scans the
         // runs' sums; every workgroup of the ring computes the same offsets
         const int per = (G + kDtBS - 1) / kDtBS, u0 = min(tid * per, G), u1 = min(u0 + per, G);
         double v[2] = {0.0, 0.0};
         for (int u = u0; u < u1; ++u) {
-            v[0] += r.tot[u];
-            v[1] += r.tot[G + u];
+            v[0] += tot[u];
+            v[1] += tot[G + u];
         }
         block_exscan<kDtBS, 2>(v, lds);
         for (int u = u0; u < u1; ++u) {
             dt_off[u] = v[0];
             dt_off[G + u] = v[1];
-            v[0] += r.tot[u];
-            v[1] += r.tot[G + u];
+            v[0] += tot[u];
+            v[1] += tot[G + u];
         }
         __syncthreads();
     }
-    auto S = [&](int k, int comp) {  // inclusive global prefix of element k (k = -1: 0)
+    auto prefix = [&](int k, int comp) {  // inclusive global prefix of element k (k = -1: 0)
         if (k < 0) return 0.0;
-        const double o = local ? dt_off[comp * G + k / kDtT] : r.tot[comp * G + k / kDtT];
-        return o + r.pre[comp * n + k];
+        const double o = local ? dt_off[comp * G + k / T] : tot[comp * G + k / T];
+        return o + pre[comp * n + k];
     };
-    double es[1] = {0.0};
+    const double* y = r.y[c.ypar];
+    const double* zs = S == 0 ? y : (S == 6 ? r.y[c.ypar ^ 1] : r.Z);
+    double* kq[S + 1];
 #pragma unroll
-    for (int e = 0; e < kDtEPT; ++e) {
+    for (int q = 0; q <= S; ++q) kq[q] = r.k[(c.f + q) % 7];
+    double* zo = S == 5 ? r.y[c.ypar ^ 1] : r.Z;
+    double es[1] = {0.0};
+    double2 xn[EPT];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
         const int i = t0 + e * kDtBS + tid;
+        xn[e] = make_double2(0.0, 0.0);
         if (i >= n) continue;
-        // the stage value as the map launch computed it
-        const double* zs = s == 0 ? r.y[c.ypar] : (s == 6 ? r.y[c.ypar ^ 1] : r.Z);
+        // own operands of the next stage value, in flight during the neighbour sums
+        double yv[V], av[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const int64_t o = (int64_t)v * n + i;
+            yv[v] = kNext || S == 6 ? y[o] : 0.0;
+            av[v] = 0.0;
+            if constexpr (kNext) {
+#pragma unroll
+                for (int q = 0; q < S; ++q) av[v] = fma(kDpA[S + 1][q], kq[q][o], av[v]);
+            }
+            if constexpr (S == 6) {
+#pragma unroll
+                for (int q = 0; q < S; ++q) av[v] = fma(kDpE[q], kq[q][o], av[v]);
+            }
+        }
         double z[V];
 #pragma unroll
         for (int v = 0; v < V; ++v) z[v] = zs[(int64_t)v * n + i];
-        // the element's own map: stored by the map launch where the rows gather
+        // the element's own map: stored by the launch before where the rows gather
         // maps anyway, else recomputed from the same stage value (same bits)
-        const double2 x = TOPO == ND_LINKS ? ((const double2*)r.M)[i] : M::map(z);
+        const double2 x = TOPO == ND_LINKS ? ((const double2*)r.M[b])[i] : M::map(z);
         double2 W;
         if constexpr (TOPO == ND_RING) {
             const int lo = i - P, hi = i + P;
             double w0, w1;
             if (lo < 0) {
-                w0 = S(hi, 0) + (S(n - 1, 0) - S(lo + n - 1, 0));
-                w1 = S(hi, 1) + (S(n - 1, 1) - S(lo + n - 1, 1));
+                w0 = prefix(hi, 0) + (prefix(n - 1, 0) - prefix(lo + n - 1, 0));
+                w1 = prefix(hi, 1) + (prefix(n - 1, 1) - prefix(lo + n - 1, 1));
             } else if (hi >= n) {
-                w0 = (S(n - 1, 0) - S(lo - 1, 0)) + S(hi - n, 0);
-                w1 = (S(n - 1, 1) - S(lo - 1, 1)) + S(hi - n, 1);
+                w0 = (prefix(n - 1, 0) - prefix(lo - 1, 0)) + prefix(hi - n, 0);
+                w1 = (prefix(n - 1, 1) - prefix(lo - 1, 1)) + prefix(hi - n, 1);
             } else {
-                w0 = S(hi, 0) - S(lo - 1, 0);
-                w1 = S(hi, 1) - S(lo - 1, 1);
+                w0 = prefix(hi, 0) - prefix(lo - 1, 0);
+                w1 = prefix(hi, 1) - prefix(lo - 1, 1);
             }
             W = make_double2(w0 - x.x, w1 - x.y);
         } else {
             // row i = (V XOR D[C_i]) shifted by i: V's positions, then the entry's
             // signed positions, divided by the row's link count
-            const double2* __restrict__ mp = (const double2*)r.M;
+            const double2* __restrict__ mp = (const double2*)r.M[b];
             double w0 = 0.0, w1 = 0.0;
 #pragma unroll 8
             for (int q = 0; q < d.lnv; ++q) {
@@ -553,22 +607,27 @@ __global__ __launch_bounds__(kDtBS) void k_dt_rhs(const DtNet* __restrict__ R, c
         }
         double k[V];
         M::rhs(d, z, x, W, k);
-        double* ko = r.k[(c.f + s) % 7];
+        double zn[V];
 #pragma unroll
-        for (int v = 0; v < V; ++v) ko[(int64_t)v * n + i] = k[v];
-        if (s == 6 && rtol > 0.0) {
-            const double* y = r.y[c.ypar];
-#pragma unroll
-            for (int v = 0; v < V; ++v) {
-                double er = 0.0;
-                for (int q = 0; q < 7; ++q) er += kDpE[q] * r.k[(c.f + q) % 7][(int64_t)v * n + i];
-                er *= c.hs;
-                const double sc = atol + rtol * fmax(fabs(y[(int64_t)v * n + i]), fabs(z[v]));
-                es[0] += (er / sc) * (er / sc);
+        for (int v = 0; v < V; ++v) {
+            const int64_t o = (int64_t)v * n + i;
+            kq[S][o] = k[v];
+            if constexpr (kNext) {
+                zn[v] = fma(c.hs, fma(kDpA[S + 1][S], k[v], av[v]), yv[v]);
+                zo[o] = zn[v];
+            }
+            if constexpr (S == 6) {
+                if (rtol > 0.0) {
+                    const double er = fma(kDpE[6], k[v], av[v]) * c.hs;
+                    const double sc = fma(rtol, fmax(fabs(yv[v]), fabs(z[v])), atol);
+                    es[0] += (er / sc) * (er / sc);
+                }
             }
         }
+        if constexpr (kNext) xn[e] = M::map(zn);
     }
-    if (s == 6) {
+    if constexpr (kNext) dt_leave<TOPO>(r, b ^ 1, wk.y, xn, lds);
+    if constexpr (S == 6) {
         block_sum<kDtBS, 1>(es, lds);
         if (tid == 0) r.errp[wk.y] = es[0];
     }
@@ -642,21 +701,34 @@ __global__ __launch_bounds__(kWave) void k_dt_control(const DtNet* __restrict__ 
     *r.ctl = c;
 }
 
-// Dense output of the step just accepted: for each of its outputs, the
-// continuous extension on the tile's elements (the state, when requested) and
-// the tile's sums of the order parameter's unit vectors.
-template <int MODEL>
+// Dense output of the step just accepted: the continuous extension on the tile's
+// elements at each of its outputs (the state, when requested) and the tile's sums of
+// the order parameter's unit vectors.  The slopes are read once for all outputs.
+template <int MODEL, int TOPO>
 __global__ __launch_bounds__(kDtBS) void k_dt_emit(const DtNet* __restrict__ R, const int2* __restrict__ work,
                                                    double t_out) {
     using M = RingModel<MODEL, double>;
-    constexpr int V = M::V, NW = kDtBS / kWave;
+    constexpr int V = M::V, NW = kDtBS / kWave, EPT = DtTile<TOPO>::EPT, T = DtTile<TOPO>::T;
     __shared__ double lds[2 * NW];
     const int2 wk = work[blockIdx.x];
     const DtNet& r = R[wk.x];
     const DtCtl c = *r.ctl;
     if (c.out_hi <= c.out_lo) return;
-    const int n = r.n, t0 = wk.y * kDtT, tid = threadIdx.x;
+    const int n = r.n, t0 = wk.y * T, tid = threadIdx.x;
     const double* y = r.y[c.ypar_prev];
+    const bool start = c.out_lo == 0;  // output 0 is the initial state (no stage slopes yet)
+    double yv[EPT][V], kv[EPT][V][7];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+        const int i = t0 + e * kDtBS + tid;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            yv[e][v] = i < n ? y[(int64_t)v * n + i] : 0.0;
+#pragma unroll
+            for (int q = 0; q < 7; ++q)
+                kv[e][v][q] = i < n && !start ? r.k[(c.f_prev + q) % 7][(int64_t)v * n + i] : 0.0;
+        }
+    }
     for (int64_t ko = c.out_lo; ko < c.out_hi; ++ko) {
         const double theta = fmin(((double)ko * t_out - c.t_prev) / c.hs_prev, 1.0);
         double wt[7];
@@ -667,16 +739,17 @@ __global__ __launch_bounds__(kDtBS) void k_dt_emit(const DtNet* __restrict__ R, 
         }
         double s2[2] = {0.0, 0.0};
 #pragma unroll
-        for (int e = 0; e < kDtEPT; ++e) {
+        for (int e = 0; e < EPT; ++e) {
             const int i = t0 + e * kDtBS + tid;
             if (i >= n) continue;
             double yt[V];
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-                yt[v] = y[(int64_t)v * n + i];
-                if (theta != 0.0) {  // theta = 0: the initial state (no stage slopes yet)
+                yt[v] = yv[e][v];
+                if (theta != 0.0) {
                     double a = 0.0;
-                    for (int q = 0; q < 7; ++q) a += wt[q] * r.k[(c.f_prev + q) % 7][(int64_t)v * n + i];
+#pragma unroll
+                    for (int q = 0; q < 7; ++q) a += wt[q] * kv[e][v][q];
                     yt[v] += c.hs_prev * a;
                 }
                 if (r.Y) r.Y[ko * V * n + (int64_t)v * n + i] = yt[v];
@@ -722,23 +795,27 @@ __global__ __launch_bounds__(kDtBS) void k_dt_reduce_R(const DtNet* __restrict__
 
 using namespace nd;
 
-typedef void (*DtMapFn)(const DtNet*, const int2*);
-template <int MODEL>
-static DtMapFn dt_map_of_model(int s) {
-    switch (s) {
-        case 0: return k_dt_map<MODEL, 0>;
-        case 1: return k_dt_map<MODEL, 1>;
-        case 2: return k_dt_map<MODEL, 2>;
-        case 3: return k_dt_map<MODEL, 3>;
-        case 4: return k_dt_map<MODEL, 4>;
-        case 5: return k_dt_map<MODEL, 5>;
-        default: return k_dt_map<MODEL, 6>;
-    }
+// The tiled kernels of one model and topology.
+struct DtKernels {
+    void (*begin[2])(const DtNet*, const int2*, int);
+    void (*stage[7])(const DtNet*, const NetDesc*, const int2*, int, double, double);
+    void (*emit)(const DtNet*, const int2*, double);
+    int tile;
+};
+template <int MODEL, int TOPO>
+static DtKernels dt_kernels() {
+    return {{k_dt_begin<MODEL, TOPO, 0>, k_dt_begin<MODEL, TOPO, 1>},
+            {k_dt_stage<MODEL, TOPO, 0>, k_dt_stage<MODEL, TOPO, 1>, k_dt_stage<MODEL, TOPO, 2>,
+             k_dt_stage<MODEL, TOPO, 3>, k_dt_stage<MODEL, TOPO, 4>, k_dt_stage<MODEL, TOPO, 5>,
+             k_dt_stage<MODEL, TOPO, 6>},
+            k_dt_emit<MODEL, TOPO>,
+            DtTile<TOPO>::T};
 }
-static DtMapFn dt_map_kernel(int model, int s) {
-    if (model == ND_KURAMOTO) return dt_map_of_model<ND_KURAMOTO>(s);
-    if (model == ND_FHN) return dt_map_of_model<ND_FHN>(s);
-    return dt_map_of_model<ND_KURAMOTO_INERTIA>(s);
+template <int TOPO>
+static DtKernels dt_kernels_of(int model) {
+    if (model == ND_KURAMOTO) return dt_kernels<ND_KURAMOTO, TOPO>();
+    if (model == ND_FHN) return dt_kernels<ND_FHN, TOPO>();
+    return dt_kernels<ND_KURAMOTO_INERTIA, TOPO>();
 }
 
 // Rings beyond one workgroup: buffers per ring, the stage / controller launches
@@ -748,6 +825,8 @@ static nd_status run_adaptive_tiled(const std::vector<Net*>& nets, int model, in
                                     nd_adaptive_stats* stats, hipStream_t st, double t_out, double* Rh,
                                     int64_t r_stride, double* Yh, int64_t y_stride) {
     const bool dense = t_out > 0.0;
+    const DtKernels kern = topo == ND_RING ? dt_kernels_of<ND_RING>(model) : dt_kernels_of<ND_LINKS>(model);
+    const int64_t T = kern.tile;
     const int count = (int)nets.size();
     std::vector<DtNet> rs(count);
     std::vector<DtCtl> cs(count);
@@ -756,8 +835,8 @@ static nd_status run_adaptive_tiled(const std::vector<Net*>& nets, int model, in
     size_t bytes = 0;
     for (int b = 0; b < count; ++b) {
         const Net* nt = nets[b];
-        const int64_t n = nt->prob.n, len = nvars_of(nt->prob.model) * n, G = (n + kDtT - 1) / kDtT;
-        bytes += (size_t)(9 * len + 4 * n + 3 * G) * 8 + sizeof(DtCtl);
+        const int64_t n = nt->prob.n, len = nvars_of(nt->prob.model) * n, G = (n + T - 1) / T;
+        bytes += (size_t)(9 * len + 4 * n + 5 * G) * 8 + sizeof(DtCtl);
         if (dense) bytes += (size_t)(2 * ((int64_t)std::floor(t_end[b] / t_out) + 1) * G) * 8;
         for (int64_t t = 0; t < G; ++t) work.push_back(make_int2(b, (int)t));
     }
@@ -783,8 +862,7 @@ static nd_status run_adaptive_tiled(const std::vector<Net*>& nets, int model, in
         DtNet& r = rs[b];
         r.n = (int32_t)n;
         r.P = (int32_t)nt->prob.radius;
-        r.gather = topo == ND_LINKS;
-        r.G = (int32_t)((n + kDtT - 1) / kDtT);
+        r.G = (int32_t)((n + T - 1) / T);
         r.V = nvars_of(nt->prob.model);
         r.tend = t_end[b];
         descs[b] = nt->run_desc(dt0[b], 0);
@@ -792,9 +870,12 @@ static nd_status run_adaptive_tiled(const std::vector<Net*>& nets, int model, in
         r.y[1] = (double*)take(len * 8);
         for (int q = 0; q < 7; ++q) r.k[q] = (double*)take(len * 8);
         r.Z = (double*)take(len * 8);
-        r.M = (double*)take(2 * n * 8);
-        r.pre = (double*)take(2 * n * 8);
-        r.tot = (double*)take(2 * r.G * 8);
+        for (int b2 = 0; b2 < 2; ++b2) {  // a network needs the maps or the prefix sums
+            double* q = (double*)take(2 * n * 8);
+            r.M[b2] = topo == ND_LINKS ? q : nullptr;
+            r.pre[b2] = topo == ND_LINKS ? nullptr : q;
+            r.tot[b2] = (double*)take(2 * r.G * 8);
+        }
         r.errp = (double*)take(r.G * 8);
         r.ctl = (DtCtl*)take(sizeof(DtCtl));
         r.K = dense ? (int64_t)std::floor(t_end[b] / t_out) : -1;
@@ -834,29 +915,22 @@ static nd_status run_adaptive_tiled(const std::vector<Net*>& nets, int model, in
         else local_g = std::max(local_g, (int)r.G);
     }
     const size_t off_bytes = topo == ND_RING ? (size_t)2 * local_g * 8 : 0;
+    const dim3 grid((tiles + 7) / 8 * 8);
+    auto offsets = [&](int b) {
+        if (topo == ND_RING && long_rings) hipLaunchKernelGGL(k_dt_offsets, dim3(count), dim3(kDtBS), 0, st, d_r, b);
+    };
+    auto begin = [&](int s) {
+        hipLaunchKernelGGL(kern.begin[s], grid, dim3(kDtBS), 0, st, d_r, d_work, tiles);
+        offsets(s);
+        return hipGetLastError();
+    };
     auto stage = [&](int s) {
-        const DtMapFn map = dt_map_kernel(model, s);
-        hipLaunchKernelGGL(map, dim3(tiles), dim3(kDtBS), 0, st, d_r, d_work);
-        if (topo == ND_RING && long_rings) hipLaunchKernelGGL(k_dt_offsets, dim3(count), dim3(kDtBS), 0, st, d_r);
-        auto rhs = [&](auto kern) {
-            hipLaunchKernelGGL(kern, dim3((tiles + 7) / 8 * 8), dim3(kDtBS), off_bytes, st, d_r, d_desc, d_work, tiles, s,
-                               rtol, atol);
-        };
-        if (topo == ND_RING) {
-            if (model == ND_KURAMOTO) rhs(k_dt_rhs<ND_KURAMOTO, ND_RING>);
-            else if (model == ND_FHN) rhs(k_dt_rhs<ND_FHN, ND_RING>);
-            else rhs(k_dt_rhs<ND_KURAMOTO_INERTIA, ND_RING>);
-        } else {
-            if (model == ND_KURAMOTO) rhs(k_dt_rhs<ND_KURAMOTO, ND_LINKS>);
-            else if (model == ND_FHN) rhs(k_dt_rhs<ND_FHN, ND_LINKS>);
-            else rhs(k_dt_rhs<ND_KURAMOTO_INERTIA, ND_LINKS>);
-        }
+        hipLaunchKernelGGL(kern.stage[s], grid, dim3(kDtBS), off_bytes, st, d_r, d_desc, d_work, tiles, rtol, atol);
+        if (s >= 1 && s <= 5) offsets((s + 1) & 1);
         return hipGetLastError();
     };
     auto emit = [&]() {
-        if (model == ND_KURAMOTO) hipLaunchKernelGGL(k_dt_emit<ND_KURAMOTO>, dim3(tiles), dim3(kDtBS), 0, st, d_r, d_work, t_out);
-        else if (model == ND_FHN) hipLaunchKernelGGL(k_dt_emit<ND_FHN>, dim3(tiles), dim3(kDtBS), 0, st, d_r, d_work, t_out);
-        else hipLaunchKernelGGL(k_dt_emit<ND_KURAMOTO_INERTIA>, dim3(tiles), dim3(kDtBS), 0, st, d_r, d_work, t_out);
+        hipLaunchKernelGGL(kern.emit, dim3(tiles), dim3(kDtBS), 0, st, d_r, d_work, t_out);
         return hipGetLastError();
     };
     // outputs a run does not reach read as NaN (all bits set)
@@ -868,10 +942,12 @@ static nd_status run_adaptive_tiled(const std::vector<Net*>& nets, int model, in
     if (e == hipSuccess) e = hipMemcpyAsync(d_desc, descs.data(), bn, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemcpyAsync(d_work, work.data(), bw, hipMemcpyHostToDevice, st);
     if (e == hipSuccess && dense) e = emit();  // output 0
+    if (e == hipSuccess) e = begin(0);
     if (e == hipSuccess) e = stage(0);            // k1 = f(y)
     constexpr int kAttempts = 8;        // attempts launched between checks of the done flags
     while (e == hipSuccess) {
         for (int a = 0; a < kAttempts && e == hipSuccess; ++a) {
+            e = begin(1);
             for (int s = 1; s <= 6 && e == hipSuccess; ++s) e = stage(s);
             if (e == hipSuccess) {
                 hipLaunchKernelGGL(k_dt_control, dim3(count), dim3(kWave), 0, st, d_r, rtol, max_steps,

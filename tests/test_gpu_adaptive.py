@@ -362,3 +362,33 @@ def test_adaptive_ring_at_wave_and_capacity_edges(nd, model, n, P):
     ref, t, acc, rej, hnext = O.run_dopri(onet, y0, 1.0, 1e-8, 1e-10, 1e-3)
     assert (st.accepted, st.rejected) == (acc, rej)
     assert normwise(y, ref, nv) < 1e-10
+
+
+@pytest.mark.parametrize("n", [5, 255, 256, 257, 513])
+@pytest.mark.parametrize("model", ["kuramoto", "fhn", "inertia"])
+def test_adaptive_links_at_tile_edges(nd, model, n):
+    """Coupling matrices whose last tile is full, ragged or alone, with rows that
+    differ from the common pattern (every seventh has one link less, row 2 none): the
+    oracle's steps and, as for the rings above, its state to 1e-10; the dense output
+    ends at that state to the same bound."""
+    print(f"case adaptive links edges {model} n={n}", flush=True)
+    rows = [[] if i == 2 else sorted({(i + q) % n for q in ((1, 3) if i % 7 == 0 else (1, 2, 3))}) for i in range(n)]
+    rp = np.cumsum([0] + [len(r) for r in rows]).astype(np.int32)
+    col = np.array([j for r in rows for j in r], dtype=np.int32)
+    code, ocode, prm, nv = {"kuramoto": (nd.ND_KURAMOTO, O.KURAMOTO, KUR, 1), "fhn": (nd.ND_FHN, O.FHN, FHN, 2),
+                            "inertia": (nd.ND_KURAMOTO_INERTIA, O.INERTIA, INERT, 2)}[model]
+    y0 = (inputs.kuramoto_phases(n, n) if model == "kuramoto" else inputs.fhn_circle(n, n) if model == "fhn" else
+          np.concatenate([inputs.kuramoto_phases(n, n), inputs.uniform_range(n, inputs.TAG_MISC, n, -0.5, 0.5)]))
+    p = nd.problem(code, nd.ND_LINKS, n, prm, row_ptr=rp, col=col)
+    (y,), (st,) = run_gpu(nd, [p], [y0], [1.0], [1e-3], 1e-8, 1e-10)
+    ref, t, acc, rej, _ = O.run_dopri(O.links(ocode, n, rp, col, np.array(prm)), y0, 1.0, 1e-8, 1e-10, 1e-3)
+    assert (st.accepted, st.rejected) == (acc, rej) and st.t == t
+    assert normwise(y, ref, nv) < 1e-10
+    h = nd.nd_create(p)
+    try:
+        nd.nd_set_state(h, y0, on_device=0)
+        (std,), R, Y = nd.nd_run_adaptive_dense([h], [1.0], [1e-3], 1e-8, 1e-10, 0.25, state_len=nv * n)
+    finally:
+        nd.nd_destroy(h)
+    assert (std.accepted, std.rejected) == (acc, rej)
+    assert normwise(Y[0].reshape(5, nv * n)[4], ref, nv) < 1e-10
