@@ -52,6 +52,9 @@ struct Net {
     // out of date (read as clear) and the next run clears it with its descriptors, so
     // setting a state launches nothing besides the copy
     bool status_stale = false;
+    // a state set or a run of this network was recorded into a graph: its replays pass
+    // the host by, so from then on setting a state clears the word at once
+    bool captured = false;
     int32_t* status_host = nullptr;  // pinned copy, read after a synchronising call
     hipEvent_t last_ev = nullptr;    // recorded after the last work enqueued for this network alone
     std::shared_ptr<RunEvent> batch_ev;  // else the event of the batch that last ran it

@@ -1052,6 +1052,13 @@ __global__ void k_put_desc(NetDesc* dst, NetDesc d) {
     if (d.fresh) *d.status = 0;
 }
 __global__ void k_clear_status(int32_t* status) { *status = 0; }
+
+// Work enqueued on st is being recorded into a graph (the default stream never is).
+static bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return st && hipStreamIsCapturing(st, &c) == hipSuccess && c == hipStreamCaptureStatusActive;
+}
+
 __global__ void k_clear_fresh(const NetDesc* D, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n && D[i].fresh) *D[i].status = 0;
@@ -1178,6 +1185,8 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
     nd_status s;
     for (int i = 0; i < count; ++i)
         if ((s = nets[i]->prepare_observe(steps[i], obs ? &obs[i] : nullptr))) return s;
+    if (capturing(st))
+        for (int i = 0; i < count; ++i) nets[i]->captured = true;
     // group by kernel class
     std::map<std::tuple<int, int, int, int, int, int, int>, std::vector<int>> groups;
     for (int i = 0; i < count; ++i) {
@@ -1385,6 +1394,8 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
     if (s) return s;
     for (int i = 0; i < count; ++i)
         if ((s = nets[i]->prepare_observe(steps[i], obs ? &obs[i] : nullptr, false))) return s;
+    if (capturing(st))
+        for (int i = 0; i < count; ++i) nets[i]->captured = true;
     NetDesc* descs = (NetDesc*)base;
     int* counts = (int*)(base + kNaDescBytes);
     int2* works = (int2*)(base + kNaDescBytes + kNaCountBytes);
@@ -1510,13 +1521,14 @@ nd_status nd_set_state(nd_handle h, const double* y, int64_t len, int32_t on_dev
     HIPC(hipMemcpyAsync(n->tmpl.y[n->ypar], y, len * 8, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st));
     // A new state starts with a clean status word: the next run clears it with its
     // descriptors instead of a launch here (2 us a call: 512 rings of 1,024 set and run
-    // 20.2 -> 19.2 ms, adaptively 10.6 -> 9.1 ms).  A graph under capture replays
-    // without the next run's host side, so the clear is recorded there.
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (st) HIPC(hipStreamIsCapturing(st, &cap));
-    if (cap == hipStreamCaptureStatusActive) {
+    // 20.2 -> 19.2 ms, adaptively 10.6 -> 9.1 ms).  Graphs replay without the host side
+    // of the run or of this call, so networks that take part in one get the launch.
+    const bool cap = capturing(st);
+    if (cap || n->captured) {
+        n->captured = true;
         hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(1), 0, st, n->status_dev);
         HIPC(hipGetLastError());
+        if (!cap) n->status_stale = false;
     } else {
         n->status_stale = true;
     }

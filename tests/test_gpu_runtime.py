@@ -219,6 +219,47 @@ def test_new_state_resets_only_its_own_status(nd, kind, batch):
         nd.nd_destroy(hb)
 
 
+@pytest.mark.parametrize("kind", ["ring_resident", "ring_tiled", "cube"])
+def test_status_over_graph_replays(nd, kind):
+    """A run recorded into a graph: every replay from a non-finite state is reported,
+    every replay from a new finite state is clean and equals the eager run."""
+    import torch
+    p, y0, dt = _cases(nd)[kind]
+    bad = y0.copy()
+    bad[len(bad) // 3] = np.nan
+    good, bad = torch.from_numpy(y0).cuda(), torch.from_numpy(bad).cuda()
+    st = torch.cuda.Stream()
+    h = nd.nd_create(p)
+    try:
+        with torch.cuda.stream(st):
+            nd.nd_set_state(h, good, stream=st)
+            nd.nd_run_batch_noalloc([h], [dt], [4], stream=st)
+            ref = torch.empty_like(good)
+            nd.nd_get_state(h, ref, stream=st)
+            nd.nd_sync(h, stream=st)
+            nd.nd_set_state(h, good, stream=st)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            nd.nd_run_batch_noalloc([h], [dt], [4], stream=st)  # an even number: the state's buffer stays the same
+        with torch.cuda.stream(st):
+            for y in (good, bad, good, bad, bad, good):
+                nd.nd_set_state(h, y, stream=st)
+                g.replay()
+                if y is bad:
+                    with pytest.raises(nd.NDError) as ei:
+                        nd.nd_sync(h, stream=st)
+                    assert ei.value.status == nd.ND_ERR_NUMERIC
+                else:
+                    nd.nd_sync(h, stream=st)
+                    out = torch.empty_like(good)
+                    nd.nd_get_state(h, out, stream=st)
+                    nd.nd_sync(h, stream=st)
+                    assert torch.equal(out, ref)
+    finally:
+        nd.nd_destroy(h)
+
+
 def test_server_fails_a_diverging_request_alone(nd):
     """An FHN request with a step far beyond the model's stability limit blows up
     within a few steps; the server fails it at the next chunk boundary with
