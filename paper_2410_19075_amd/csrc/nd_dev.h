@@ -72,9 +72,9 @@ struct NetDesc {
     int64_t g0;         // run step index at the start of the current chunk
     int64_t nsteps;     // steps still to do at the start of the current chunk
     int32_t ypar;       // which y buffer holds the state at the start of the chunk
-    int32_t fresh;      // a new state was set: the run starts by clearing the status word
-    int32_t* status;    // the network's status word: stage 4 stores 1 there when it produces a
-                        // non-finite state value (cleared by the first run after a new state)
+    int32_t tag;        // number of the state the run starts from (Net::status_tag)
+    int32_t* status;    // the network's status word: stage 4 stores the tag there when it produces
+                        // a non-finite state value
 };
 
 
@@ -94,9 +94,9 @@ __device__ __forceinline__ const ND_GLOBAL T* gp(const T* p) {
 }
 
 // Flag a non-finite new state value in the network's status word (a plain
-// store of 1 from every lane that sees one; the host reads the word back).
+// store of the tag from every lane that sees one; the host reads the word back).
 __device__ __forceinline__ void flag_nonfinite(const NetDesc& d, double v) {
-    if (!__builtin_isfinite(v)) *gp(d.status) = 1;
+    if (!__builtin_isfinite(v)) *gp(d.status) = d.tag;
 }
 
 __device__ __forceinline__ int ring_wrap32(int i, int n) {

@@ -48,12 +48,15 @@ struct Net {
     double* mv_dev = nullptr;
     NetDesc* solo_desc = nullptr;  // descriptor for running this network alone
     int32_t* status_dev = nullptr;   // status word the stage kernels flag (non-finite state)
-    // a new state was set and no run has started since: the device's status word is
-    // out of date (read as clear) and the next run clears it with its descriptors, so
-    // setting a state launches nothing besides the copy
-    bool status_stale = false;
+    // number of the current state: every nd_set_state takes the next one, a run's
+    // descriptor carries it, a kernel that flags the state stores it in the status word,
+    // and a word that holds another number belongs to an earlier state.  So setting a
+    // state launches nothing besides the copy, and nothing has to run before the word
+    // reads as clear.
+    int32_t status_tag = 1;
     // a state set or a run of this network was recorded into a graph: its replays pass
-    // the host by, so from then on setting a state clears the word at once
+    // the host by and store the recorded number, so from then on the number stays and
+    // setting a state clears the word instead
     bool captured = false;
     int32_t* status_host = nullptr;  // pinned copy, read after a synchronising call
     hipEvent_t last_ev = nullptr;    // recorded after the last work enqueued for this network alone

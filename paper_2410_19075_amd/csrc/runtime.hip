@@ -895,7 +895,7 @@ NetDesc Net::run_desc(double dt, int64_t steps) const {
     d.g0 = 0;
     d.nsteps = steps;
     d.ypar = ypar;
-    d.fresh = status_stale;
+    d.tag = status_tag;
     return d;
 }
 
@@ -1047,21 +1047,13 @@ static nd_status run_resident(const Group& g, int64_t maxsteps, hipStream_t st) 
     return ND_OK;
 }
 
-__global__ void k_put_desc(NetDesc* dst, NetDesc d) {
-    *dst = d;
-    if (d.fresh) *d.status = 0;
-}
+__global__ void k_put_desc(NetDesc* dst, NetDesc d) { *dst = d; }
 __global__ void k_clear_status(int32_t* status) { *status = 0; }
 
 // Work enqueued on st is being recorded into a graph (the default stream never is).
 static bool capturing(hipStream_t st) {
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
     return st && hipStreamIsCapturing(st, &c) == hipSuccess && c == hipStreamCaptureStatusActive;
-}
-
-__global__ void k_clear_fresh(const NetDesc* D, int n) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && D[i].fresh) *D[i].status = 0;
 }
 
 hipError_t put_desc(NetDesc* dst, const NetDesc& d, hipStream_t st) {
@@ -1228,7 +1220,6 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
             g.nwork = nullptr;
             if ((e = put_desc(g.desc, n->run_desc(dt[idx[0]], steps[idx[0]]), st)) != hipSuccess)
                 return hip_fail(e, "descriptor upload");
-            n->status_stale = false;
         } else {
             const size_t bd = idx.size() * sizeof(NetDesc), bw = (size_t)nwork * sizeof(int2);
             Staging* sb = nullptr;
@@ -1251,13 +1242,6 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
             g.desc = (NetDesc*)scratch;
             g.work = (int2*)((char*)scratch + bd);
             g.nwork = (int*)((char*)scratch + bd + bw);
-            bool fresh = false;
-            for (int q : idx) fresh = fresh || nets[q]->status_stale;
-            if (fresh) {
-                hipLaunchKernelGGL(k_clear_fresh, dim3((g.ndesc + 255) / 256), dim3(256), 0, st, g.desc, g.ndesc);
-                if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "status words");
-            }
-            for (int q : idx) nets[q]->status_stale = false;
         }
         const Net* n0 = nets[idx[0]];
         const int cfg_grid = n0->cfg.grid;
@@ -1440,7 +1424,6 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
             const Net* n = nets[i];
             if ((e = put_desc(g.desc + g.ndesc, n->run_desc(dt[i], steps[i]), st)) != hipSuccess)
                 return hip_fail(e, "descriptor upload");
-            nets[i]->status_stale = false;
             ++g.ndesc;
             g.mv = g.mv || n->mv_start >= 0;
             g.edges = std::max(g.edges, n->csr_edges);
@@ -1519,18 +1502,17 @@ nd_status nd_set_state(nd_handle h, const double* y, int64_t len, int32_t on_dev
     if (len != want) return fail(ND_ERR_INVALID_ARG, "state length %lld, expected %lld", (long long)len, (long long)want);
     hipStream_t st = (hipStream_t)stream;
     HIPC(hipMemcpyAsync(n->tmpl.y[n->ypar], y, len * 8, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st));
-    // A new state starts with a clean status word: the next run clears it with its
-    // descriptors instead of a launch here (2 us a call: 512 rings of 1,024 set and run
-    // 20.2 -> 19.2 ms, adaptively 10.6 -> 9.1 ms).  Graphs replay without the host side
-    // of the run or of this call, so networks that take part in one get the launch.
-    const bool cap = capturing(st);
-    if (cap || n->captured) {
-        n->captured = true;
+    // A new state starts with a clean status word: it takes the next number, which no
+    // earlier run stores, instead of a launch that clears the word (2 us a call: 512
+    // rings of 1,024 set and run 20.2 -> 19.2 ms, adaptively 10.6 -> 9.1 ms).  Graphs
+    // replay without the host side of the run or of this call, so networks that take
+    // part in one keep their number and get the launch (so do those out of numbers).
+    if (capturing(st)) n->captured = true;
+    if (n->captured || n->status_tag == INT32_MAX) {
         hipLaunchKernelGGL(k_clear_status, dim3(1), dim3(1), 0, st, n->status_dev);
         HIPC(hipGetLastError());
-        if (!cap) n->status_stale = false;
     } else {
-        n->status_stale = true;
+        ++n->status_tag;
     }
     if (!on_device) HIPC(hipStreamSynchronize(st));
     return n->touch(st);
@@ -1541,7 +1523,7 @@ nd_status nd_set_state(nd_handle h, const double* y, int64_t len, int32_t on_dev
 static nd_status sync_status(Net* n, hipStream_t st, const char* what) {
     HIPC(hipMemcpyAsync(n->status_host, n->status_dev, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPC(hipStreamSynchronize(st));
-    if (*n->status_host && !n->status_stale)
+    if (*n->status_host == n->status_tag)
         return fail(ND_ERR_NUMERIC, "%s: the state holds a non-finite value (a run produced NaN or Inf)", what);
     return ND_OK;
 }

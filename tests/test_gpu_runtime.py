@@ -260,6 +260,80 @@ def test_status_over_graph_replays(nd, kind):
         nd.nd_destroy(h)
 
 
+@pytest.mark.parametrize("kind", ["ring_resident", "ring_tiled", "cube", "csr"])
+@pytest.mark.parametrize("replay", [False, True])
+@pytest.mark.parametrize("record_set", [False, True])
+def test_status_of_a_run_recorded_after_a_failure(nd, kind, replay, record_set):
+    """A network fails, gets a finite state, and a run (with or without its own state
+    set) is recorded into a graph: the state reads clean before any replay, the
+    first replay and an eager run in its place are clean and equal the run of a
+    network that never failed, and later failures are reported all the same."""
+    import torch
+    p, y0, dt = _cases(nd)[kind]
+    bad = y0.copy()
+    bad[len(bad) // 3] = np.nan
+    good, bad = torch.from_numpy(y0).cuda(), torch.from_numpy(bad).cuda()
+    ref, out = torch.empty_like(good), torch.empty_like(good)
+    host = np.empty_like(y0)
+    st = torch.cuda.Stream()
+    h, hr = nd.nd_create(p), nd.nd_create(p)
+
+    def run():
+        nd.nd_run_batch_noalloc([h], [dt], [4], stream=st)  # an even number: the state's buffer stays the same
+
+    def fails():
+        with pytest.raises(nd.NDError) as ei:
+            nd.nd_sync(h, stream=st)
+        assert ei.value.status == nd.ND_ERR_NUMERIC
+
+    def clean():
+        nd.nd_sync(h, stream=st)
+        nd.nd_get_state(h, out, stream=st)
+        nd.nd_sync(h, stream=st)
+        assert torch.equal(out, ref)
+
+    try:
+        with torch.cuda.stream(st):
+            nd.nd_set_state(hr, good, stream=st)
+            nd.nd_run_batch_noalloc([hr], [dt], [4], stream=st)
+            nd.nd_get_state(hr, ref, stream=st)
+            nd.nd_set_state(h, bad, stream=st)
+            run()
+            fails()
+            nd.nd_set_state(h, good, stream=st)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            if record_set:
+                nd.nd_set_state(h, good, stream=st)
+            run()
+        with torch.cuda.stream(st):
+            nd.nd_sync(h, stream=st)
+            nd.nd_get_state(h, host, on_device=0, stream=st)
+            assert np.array_equal(host, y0)
+            if replay:
+                g.replay()
+            else:
+                run()
+            clean()
+            nd.nd_set_state(h, bad, stream=st)
+            run()
+            fails()
+            nd.nd_set_state(h, good, stream=st)
+            nd.nd_sync(h, stream=st)
+            if replay:
+                for y in (bad, good, bad, good):
+                    nd.nd_set_state(h, y, stream=st)
+                    g.replay()
+                    if y is bad and not record_set:
+                        fails()
+                    else:
+                        clean()
+    finally:
+        nd.nd_destroy(h)
+        nd.nd_destroy(hr)
+
+
 def test_server_fails_a_diverging_request_alone(nd):
     """An FHN request with a step far beyond the model's stability limit blows up
     within a few steps; the server fails it at the next chunk boundary with
