@@ -161,6 +161,9 @@ __global__ __launch_bounds__(ROWS) __attribute__((amdgpu_waves_per_eu(4))) void 
             __syncthreads();
         }
         if (tid < nrows) gp(d.acc_part)[(int64_t)x * n + r0 + tid] = a;
+        // rb is rewritten by the next work item, and an item without edges has passed
+        // no barrier since its row bounds were read
+        lds_barrier();
     }
 }
 

@@ -263,3 +263,38 @@ def test_hh_batch_of_mixed_sizes_and_degrees(nd):
     finally:
         for h in hs:
             nd.nd_destroy(h)
+
+
+@pytest.mark.parametrize("n", [3000, 70001])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_hh_banded_graph_on_a_small_grid(nd, n, prec):
+    """Rows with sources within 10 places, every 64th without any: nearly all (row
+    tile, source block) items have no edges.  Eight workgroups that take many items
+    each give the bits of one workgroup per item; FP64 also against the oracle."""
+    rng = np.random.default_rng(n)
+    deg = np.where(np.arange(n) % 64 == 0, 0, 6)
+    rp = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    off = np.array([-10, -4, -1, 2, 3, 10])
+    col = ((np.arange(n)[deg > 0, None] + off[None, :]) % n).astype(np.int32).ravel()
+    w = rng.random(col.size) * 0.1
+    iapp, y0 = inputs.hh_iapp(3, n), inputs.hh_state(3, n)
+    p = nd.problem(nd.ND_HH, nd.ND_CSR, n, HH_PRM, precision=prec, row_ptr=rp, col=col, weight=w, per_elem=iapp)
+    got = []
+    for grid in (0, 8):
+        print(f"case hh banded n={n} prec={prec} grid={grid}", flush=True)
+        h = nd.nd_create(p)
+        try:
+            c = nd.nd_get_config(h)
+            c.grid = grid
+            nd.nd_set_config(h, c)
+            nd.nd_set_state(h, y0, on_device=0)
+            nd.nd_run(h, 0.01, 5)
+            y = np.empty_like(y0)
+            nd.nd_get_state(h, y, on_device=0)
+            got.append(y)
+        finally:
+            nd.nd_destroy(h)
+    assert np.array_equal(got[0], got[1])
+    if prec == 0:
+        ref, _, _ = O.run(O.csr(n, rp, col, w, HH_PRM, iapp), y0, 0.01, 5)
+        assert normwise(got[0], ref) < 1e-12
