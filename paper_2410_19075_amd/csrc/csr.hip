@@ -10,7 +10,7 @@
 //
 // Per stage the activations s_j = S(V_j) of the stage values are computed
 // once per neuron by the previous stage (the exchanged quantity), and each
-// work item (csr_rows target rows) does:
+// work item (csr_rows target rows, NetDesc::tile) does:
 //   phase A: the in-edges are split into 8 source blocks (one per XCD); per
 //            (row tile, block) the tile's edges are streamed coalesced, the
 //            products w_e s_src(e) are formed in double and every row's
@@ -59,9 +59,15 @@ __device__ __forceinline__ T synapse(const double* p, double V) {
     return (T)1 / ((T)1 + exp(-((T)V - (T)p[8]) / (T)p[9]));
 }
 
+// The workgroup size BS is the most rows of a work item in the launch.  Networks of
+// 256 and of 512 rows share the launches of BS = 512; the sums do not depend on BS.
+// Six networks of 2000 to 2e5 neurons, us per step in two sets of launches, one after
+// the other / in one: degree 20 230 / 200, degree 100 538 / 554 (the 512-row items' LDS
+// holds back the smaller networks' workgroups).
+
 // Activations of the run's initial state (networks with g0 == 0).
-template <class KT, int ROWS>
-__global__ __launch_bounds__(ROWS) void k_csr_prologue(const NetDesc* __restrict__ D, const int2* __restrict__ work,
+template <class KT, int BS>
+__global__ __launch_bounds__(BS) void k_csr_prologue(const NetDesc* __restrict__ D, const int2* __restrict__ work,
                                                      const int* __restrict__ nwork_p) {
     const int nwork = work_count(D, nwork_p);
     // one row tile per workgroup: the tile's work items are 8 consecutive
@@ -71,12 +77,13 @@ __global__ __launch_bounds__(ROWS) void k_csr_prologue(const NetDesc* __restrict
         const int2 wk = work_at(work, v * kSrcBlocks);
         const NetDesc& d = D[wk.x];
         if (d.g0 != 0 || d.nsteps <= 0) continue;
-        const int64_t i = (int64_t)(wk.y / kSrcBlocks) * ROWS + threadIdx.x;
-        if (i < d.n) gp((KT*)d.sx[0])[i] = (KT)synapse<KT>(d.p, gp(d.y[d.ypar])[i]);
+        const int rows = d.tile;
+        const int64_t i = (int64_t)(wk.y / kSrcBlocks) * rows + threadIdx.x;
+        if ((int)threadIdx.x < rows && i < d.n) gp((KT*)d.sx[0])[i] = (KT)synapse<KT>(d.p, gp(d.y[d.ypar])[i]);
     }
 }
 
-// Phase A: synaptic partial sums of one source block for ROWS target rows.
+// Phase A: synaptic partial sums of one source block for a tile of target rows.
 // Work item (row tile t, block x) is entry 8t + x; with the work map aligned
 // to multiples of 8 and the grid a multiple of 8, block x always lands on XCD x
 // (workgroups go to the XCDs round-robin), whose L2 then holds that block's
@@ -93,12 +100,11 @@ __global__ __launch_bounds__(ROWS) void k_csr_prologue(const NetDesc* __restrict
 // Measured per stage with the update (FP64 / FP32-bulk, degree 100): 2e5 neurons
 // 73 / 52 us (109 / 86 us in row order), of which the edge stream at the card's
 // copy rate is 49 / 32 us; 1e6 neurons 458 / 346 us (560 / 558 us).
-template <class KT, int U, int ROWS>
-__global__ __launch_bounds__(ROWS) __attribute__((amdgpu_waves_per_eu(4))) void k_csr_gather(const NetDesc* __restrict__ D, const int2* __restrict__ work,
-                                                         const int* __restrict__ nwork_p, int stage, int j) {
-    constexpr int BS = ROWS;
+template <class KT, int U, int BS>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_csr_gather(const NetDesc* __restrict__ D, const int2* __restrict__ work,
+                                                       const int* __restrict__ nwork_p, int stage, int j) {
     extern __shared__ double prod[];  // the largest chunk of the group's networks
-    __shared__ int64_t rb[ROWS + 1];
+    __shared__ int64_t rb[BS + 1];
     const int nwork = work_count(D, nwork_p);
     const int tid = threadIdx.x;
     for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
@@ -107,8 +113,9 @@ __global__ __launch_bounds__(ROWS) __attribute__((amdgpu_waves_per_eu(4))) void 
         if (j >= d.nsteps) continue;  // uniform over the block
         const int64_t n = d.n;
         const int x = wk.y % kSrcBlocks;
-        const int64_t r0 = (int64_t)(wk.y / kSrcBlocks) * ROWS;
-        const int nrows = (int)min((int64_t)ROWS, n - r0);
+        const int rows = d.tile;  // at most BS
+        const int64_t r0 = (int64_t)(wk.y / kSrcBlocks) * rows;
+        const int nrows = (int)min((int64_t)rows, n - r0);
         const ND_GLOBAL int64_t* __restrict__ bp = gp(d.row_ptr) + (int64_t)x * (n + 1) + r0;
         const ND_GLOBAL KT* __restrict__ wt = gp((const KT*)d.w);
         const bool packed = csr_packed(n);  // uniform
@@ -170,8 +177,8 @@ __global__ __launch_bounds__(ROWS) __attribute__((amdgpu_waves_per_eu(4))) void 
 // Phase B: one thread per neuron sums the source-block partials (fixed order),
 // evaluates the HH right-hand side, does the 13-access RK bookkeeping and
 // writes S of its next stage value.
-template <class KT, int STAGE, int ROWS>
-__global__ __launch_bounds__(ROWS) void k_csr_update(const NetDesc* __restrict__ D, const int2* __restrict__ work,
+template <class KT, int STAGE, int BS>
+__global__ __launch_bounds__(BS) void k_csr_update(const NetDesc* __restrict__ D, const int2* __restrict__ work,
                                                    const int* __restrict__ nwork_p, int j) {
     constexpr int stage = STAGE;
     const int nwork = work_count(D, nwork_p);
@@ -181,8 +188,9 @@ __global__ __launch_bounds__(ROWS) void k_csr_update(const NetDesc* __restrict__
         const NetDesc& d = D[wk.x];
         if (j >= d.nsteps) continue;
         const int64_t n = d.n;
-        const int64_t i = (int64_t)(wk.y / kSrcBlocks) * ROWS + tid;
-        if (i >= n) continue;
+        const int rows = d.tile;
+        const int64_t i = (int64_t)(wk.y / kSrcBlocks) * rows + tid;
+        if (tid >= rows || i >= n) continue;
         const int par = (d.ypar + j) & 1;
         const ND_GLOBAL double* __restrict__ y = gp(d.y[par]);
         const ND_GLOBAL KT* __restrict__ kp =
@@ -233,36 +241,36 @@ __global__ __launch_bounds__(ROWS) void k_csr_update(const NetDesc* __restrict__
 }
 
 // ------------------------------------------------------------------ launch
-template <class KT, int U, int ROWS>
+template <class KT, int U, int BS>
 static void csr_entry_l(CsrLaunch* r) {
-    r->gather = k_csr_gather<KT, U, ROWS>;
-    r->update[0] = k_csr_update<KT, 1, ROWS>;
-    r->update[1] = k_csr_update<KT, 2, ROWS>;
-    r->update[2] = k_csr_update<KT, 3, ROWS>;
-    r->update[3] = k_csr_update<KT, 4, ROWS>;
-    r->prologue = k_csr_prologue<KT, ROWS>;
-    r->rows = ROWS;
+    r->gather = k_csr_gather<KT, U, BS>;
+    r->update[0] = k_csr_update<KT, 1, BS>;
+    r->update[1] = k_csr_update<KT, 2, BS>;
+    r->update[2] = k_csr_update<KT, 3, BS>;
+    r->update[3] = k_csr_update<KT, 4, BS>;
+    r->prologue = k_csr_prologue<KT, BS>;
+    r->block = BS;
 }
 
-template <class KT, int ROWS>
+template <class KT, int BS>
 static bool csr_entry(int ept, CsrLaunch* r) {
     switch (ept) {
-        case 2: csr_entry_l<KT, 2, ROWS>(r); return true;
-        case 4: csr_entry_l<KT, 4, ROWS>(r); return true;
-        case 8: csr_entry_l<KT, 8, ROWS>(r); return true;
-        case 16: csr_entry_l<KT, 16, ROWS>(r); return true;
+        case 2: csr_entry_l<KT, 2, BS>(r); return true;
+        case 4: csr_entry_l<KT, 4, BS>(r); return true;
+        case 8: csr_entry_l<KT, 8, BS>(r); return true;
+        case 16: csr_entry_l<KT, 16, BS>(r); return true;
         default: return false;
     }
 }
 
-bool csr_select(int prec, int ept, int rows, CsrLaunch* out) {
-    if (rows == 256) return prec == ND_FP64 ? csr_entry<double, 256>(ept, out) : csr_entry<float, 256>(ept, out);
+bool csr_select(int prec, int ept, int block, CsrLaunch* out) {
+    if (block == 256) return prec == ND_FP64 ? csr_entry<double, 256>(ept, out) : csr_entry<float, 256>(ept, out);
     return prec == ND_FP64 ? csr_entry<double, 512>(ept, out) : csr_entry<float, 512>(ept, out);
 }
 
 hipError_t csr_launch_prologue(const CsrLaunch& L, int grid, hipStream_t s, NetDesc* D, const int2* work,
                                const int* nwork) {
-    hipLaunchKernelGGL(L.prologue, dim3((grid + kSrcBlocks - 1) / kSrcBlocks), dim3(L.rows), 0, s, D, work, nwork);
+    hipLaunchKernelGGL(L.prologue, dim3((grid + kSrcBlocks - 1) / kSrcBlocks), dim3(L.block), 0, s, D, work, nwork);
     return hipGetLastError();
 }
 
@@ -270,13 +278,13 @@ hipError_t csr_launch_stage(const CsrLaunch& L, int grid, int edges, hipStream_t
                             const int* nwork, int stage, int j) {
     const size_t smem = (size_t)edges * sizeof(double);
     hipError_t e = hipSuccess;
-    if (smem + (L.rows + 1) * sizeof(int64_t) > 64 * 1024)
+    if (smem + (L.block + 1) * sizeof(int64_t) > 64 * 1024)
         e = hipFuncSetAttribute((const void*)L.gather, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(L.gather, dim3(grid), dim3(L.rows), smem, s, D, work, nwork, stage, j);
+    hipLaunchKernelGGL(L.gather, dim3(grid), dim3(L.block), smem, s, D, work, nwork, stage, j);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(L.update[stage - 1], dim3((grid + kSrcBlocks - 1) / kSrcBlocks), dim3(L.rows), 0, s, D, work,
+    hipLaunchKernelGGL(L.update[stage - 1], dim3((grid + kSrcBlocks - 1) / kSrcBlocks), dim3(L.block), 0, s, D, work,
                        nwork, j);
     return hipGetLastError();
 }

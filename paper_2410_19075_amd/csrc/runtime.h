@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <memory>
 #include <string>
 #include <vector>
@@ -88,9 +89,12 @@ struct Net {
     nd_status create(const nd_problem* p);
     nd_status apply_config(const nd_kernel_config& c);
     int64_t work_items() const;
-    // what the kernel shape of a class depends on besides model, precision and tile:
-    // lattices the (half-)width, CSR the rows per work item
-    int shape_key() const;
+    // Networks of one kernel class share launches: model, topology, precision, tile,
+    // tile_y, lattice (half-)width, ball workgroup size.  CSR networks of one precision
+    // are one class whatever their rows per work item and edges in flight: their sums
+    // depend on neither, and the group takes one value of each (Group::take).
+    using Class = std::array<int, 7>;
+    Class kernel_class() const;
     nd_status prepare_observe(int64_t steps, const nd_observe* obs, bool may_alloc = true);
     NetDesc run_desc(double dt, int64_t steps) const;
     // chunked runs (serving): the run's step counter lives on the host and each
@@ -103,16 +107,23 @@ struct Net {
 
 // Networks of one kernel class launched together.
 struct Group {
-    int model, topo, prec, tile;
-    int tile_y, h;  // cube: y tile extent; Net::shape_key
-    int block;      // ball: workgroup size (256 or 1024)
-    int edges = kCsrChunk;  // CSR: edges of the largest chunk of its networks
-    bool mv;        // some network records the mean phase velocity
-    int ndesc;
-    int grid;
-    NetDesc* desc;  // device
-    int2* work;     // device
-    int* nwork;     // device
+    int model = 0, topo = 0, prec = 0, tile = 0;
+    int tile_y = 0, h = 0;  // cube: y tile extent, CSR: edges in flight; lattice (half-)width
+    int block = 0;          // ball, CSR: workgroup size
+    int edges = 0;          // CSR: edges of the largest chunk of its networks
+    int64_t nnz = 0;        // CSR: links of the network tile_y was taken from
+    bool mixed = false;     // CSR: its networks differ in tile_y
+    bool mv = false;        // some network records the mean phase velocity
+    int ndesc = 0;
+    int grid = 0;
+    NetDesc* desc = nullptr;  // device
+    int2* work = nullptr;     // device
+    int* nwork = nullptr;     // device
+
+    Group() = default;
+    explicit Group(const Net::Class& c);
+    // Take a network into the group: what its launches need beyond the class.
+    void take(const Net& n);
 };
 
 nd_status enqueue_chunk(const Group& g, int chunk, hipStream_t st);
@@ -191,9 +202,9 @@ struct CsrLaunch {
     void (*gather)(const NetDesc*, const int2*, const int*, int, int);
     void (*update[4])(const NetDesc*, const int2*, const int*, int);
     void (*prologue)(const NetDesc*, const int2*, const int*);
-    int rows;  // target rows per work item = threads per workgroup
+    int block;  // threads per workgroup: the most rows per work item in the launch
 };
-bool csr_select(int prec, int ept, int rows, CsrLaunch* out);
+bool csr_select(int prec, int ept, int block, CsrLaunch* out);
 hipError_t csr_launch_prologue(const CsrLaunch& L, int grid, hipStream_t s, NetDesc* D, const int2* work,
                                const int* nwork);
 hipError_t csr_launch_stage(const CsrLaunch& L, int grid, int edges, hipStream_t s, NetDesc* D, const int2* work,

@@ -837,9 +837,39 @@ nd_status Net::apply_config(const nd_kernel_config& c) {
 
 int64_t Net::work_items() const { return tmpl.G; }
 
-int Net::shape_key() const {
-    if (prob.topo == ND_CSR) return csr_rows(prob.n);
-    return prob.topo == ND_CUBE3D || prob.topo == ND_BALL3D || prob.topo == ND_DISK2D ? (int)prob.radius : 0;
+Net::Class Net::kernel_class() const {
+    if (prob.topo == ND_CSR) return {prob.model, prob.topo, prob.precision, 0, 0, 0, 0};
+    const bool ball = prob.topo == ND_BALL3D || prob.topo == ND_DISK2D;
+    return {prob.model, prob.topo, prob.precision, cfg.tile, cfg.tile_y,
+            ball || prob.topo == ND_CUBE3D ? (int)prob.radius : 0, ball ? cfg.block : 0};
+}
+
+Group::Group(const Net::Class& c)
+    : model(c[0]), topo(c[1]), prec(c[2]), tile(c[3]), tile_y(c[4]), h(c[5]), block(c[6]) {}
+
+// CSR: one set of launches for all, with the edges in flight of the network that has
+// the most links (see csr_unroll).  A set for each value, one after the other, takes
+// 129 us per step for 12 networks of 2000 neurons and degrees 5 to 100 (in one set
+// 51), 169 for 12 of 10^4 (114), 220 for four of 5 10^4 and degrees 10 to 100 (162).
+void Group::take(const Net& n) {
+    mv = mv || n.mv_start >= 0;
+    if (topo != ND_CSR) return;
+    edges = std::max(edges, n.csr_edges);
+    block = std::max(block, csr_rows(n.prob.n));
+    mixed = mixed || (tile_y && tile_y != n.cfg.tile_y);
+    if (!tile_y || n.prob.nnz > nnz) {
+        nnz = n.prob.nnz;
+        tile_y = n.cfg.tile_y;
+    }
+}
+
+// Edges in flight of a CSR launch: 16 take twice the registers of 8, which halves the
+// waves of the lighter networks where the products' LDS would allow them, i.e. beside
+// 256-row work items (us per step with 16 / 8: 12 of 10^4 120 / 114, four of 5 10^4
+// 170 / 162; all of degree 100 148 / 148).  The LDS of 512-row items binds first
+// (2000 to 10^5 neurons, degrees 10 to 100: 227 / 235).
+static int csr_unroll(const Group& g) {
+    return g.mixed && g.block == 256 ? std::min(g.tile_y, 8) : g.tile_y;
 }
 
 nd_status Net::prepare_observe(int64_t steps, const nd_observe* obs, bool may_alloc) {
@@ -985,7 +1015,8 @@ nd_status enqueue_chunk(const Group& g, int chunk, hipStream_t st) {
             return hip_fail(e, "links chunk");
     } else {
         CsrLaunch L;
-        if (!csr_select(g.prec, g.tile_y, g.h, &L)) return fail(ND_ERR_UNSUPPORTED, "no CSR kernel for %d edges per thread", g.tile_y);
+        if (!csr_select(g.prec, csr_unroll(g), g.block, &L))
+            return fail(ND_ERR_UNSUPPORTED, "no CSR kernel for %d edges per thread", csr_unroll(g));
         if ((e = csr_launch_prologue(L, grid, st, g.desc, g.work, g.nwork)) != hipSuccess) return hip_fail(e, "csr prologue");
         for (int j = 0; j < chunk; ++j)
             for (int s = 1; s <= 4; ++s)
@@ -1180,32 +1211,16 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
     if (capturing(st))
         for (int i = 0; i < count; ++i) nets[i]->captured = true;
     // group by kernel class
-    std::map<std::tuple<int, int, int, int, int, int, int>, std::vector<int>> groups;
-    for (int i = 0; i < count; ++i) {
-        if (steps[i] == 0) continue;
-        const Net* n = nets[i];
-        const int bs = (n->prob.topo == ND_BALL3D || n->prob.topo == ND_DISK2D) ? n->cfg.block : 0;
-        groups[std::make_tuple(n->prob.model, n->prob.topo, n->prob.precision, n->cfg.tile, n->cfg.tile_y,
-                               n->shape_key(), bs)]
-            .push_back(i);
-    }
+    std::map<Net::Class, std::vector<int>> groups;
+    for (int i = 0; i < count; ++i)
+        if (steps[i] > 0) groups[nets[i]->kernel_class()].push_back(i);
     for (auto& kv : groups) {
         const std::vector<int>& idx = kv.second;
-        Group g{};
-        g.model = std::get<0>(kv.first);
-        g.topo = std::get<1>(kv.first);
-        g.prec = std::get<2>(kv.first);
-        g.tile = std::get<3>(kv.first);
-        g.tile_y = std::get<4>(kv.first);
-        g.h = std::get<5>(kv.first);
-        g.block = std::get<6>(kv.first);
+        Group g(kv.first);
         g.ndesc = (int)idx.size();
         int64_t maxsteps = 0, nwork = 0;
-        g.mv = false;
-        g.edges = 0;
         for (int q : idx) {
-            g.mv = g.mv || nets[q]->mv_start >= 0;
-            g.edges = std::max(g.edges, nets[q]->csr_edges);
+            g.take(*nets[q]);
             nwork += nets[q]->work_items();
             maxsteps = std::max(maxsteps, steps[q]);
         }
@@ -1384,38 +1399,26 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
     int* counts = (int*)(base + kNaDescBytes);
     int2* works = (int2*)(base + kNaDescBytes + kNaCountBytes);
     // groups of one kernel class, in order of first appearance
-    int key[ND_NOALLOC_MAX_NETS][7];
+    Net::Class key[ND_NOALLOC_MAX_NETS];
     int grp[ND_NOALLOC_MAX_NETS];
     int ngroups = 0;
     for (int i = 0; i < count; ++i) {
         grp[i] = -1;
         if (steps[i] == 0) continue;
-        const Net* n = nets[i];
-        const bool ball = n->prob.topo == ND_BALL3D || n->prob.topo == ND_DISK2D;
-        const int k[7] = {n->prob.model, n->prob.topo, n->prob.precision, n->cfg.tile, n->cfg.tile_y,
-                          n->shape_key(), ball ? n->cfg.block : 0};
+        const Net::Class k = nets[i]->kernel_class();
         int gi = 0;
-        while (gi < ngroups && std::memcmp(key[gi], k, sizeof k) != 0) ++gi;
-        if (gi == ngroups) std::memcpy(key[ngroups++], k, sizeof k);
+        while (gi < ngroups && key[gi] != k) ++gi;
+        if (gi == ngroups) key[ngroups++] = k;
         grp[i] = gi;
     }
     int dnext = 0;
     int64_t wnext = 0;
     hipError_t e;
     for (int gi = 0; gi < ngroups; ++gi) {
-        Group g{};
-        g.model = key[gi][0];
-        g.topo = key[gi][1];
-        g.prec = key[gi][2];
-        g.tile = key[gi][3];
-        g.tile_y = key[gi][4];
-        g.h = key[gi][5];
-        g.block = key[gi][6];
+        Group g(key[gi]);
         g.desc = descs + dnext;
         g.work = works + wnext;
         g.nwork = counts + gi;
-        g.mv = false;
-        g.edges = 0;
         int64_t maxsteps = 0, nwork = 0, values = 0;
         int first = -1;
         for (int i = 0; i < count; ++i) {
@@ -1425,8 +1428,7 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
             if ((e = put_desc(g.desc + g.ndesc, n->run_desc(dt[i], steps[i]), st)) != hipSuccess)
                 return hip_fail(e, "descriptor upload");
             ++g.ndesc;
-            g.mv = g.mv || n->mv_start >= 0;
-            g.edges = std::max(g.edges, n->csr_edges);
+            g.take(*n);
             nwork += n->work_items();
             values += n->prob.n * nvars_of(n->prob.model);
             maxsteps = std::max(maxsteps, steps[i]);

@@ -57,9 +57,9 @@ namespace nd {
 using ClassKey = std::tuple<int, int, int, int, int, int, int>;
 
 static ClassKey class_key(const Net* n) {
-    const int bs = (n->prob.topo == ND_BALL3D || n->prob.topo == ND_DISK2D) ? n->cfg.block : 0;
-    return ClassKey(n->prob.model, n->prob.topo, n->prob.precision, n->cfg.tile, n->cfg.tile_y, n->shape_key(),
-                    bs);
+    if (n->prob.topo == ND_CSR)
+        return ClassKey(n->prob.model, n->prob.topo, n->prob.precision, 0, n->cfg.tile_y, 0, csr_rows(n->prob.n));
+    return std::tuple_cat(n->kernel_class());
 }
 
 struct Request {
@@ -264,6 +264,7 @@ nd_status Server::table_for(Request* r, ClassTable** out) {
     g.tile_y = std::get<4>(key);
     g.h = std::get<5>(key);
     g.block = std::get<6>(key);
+    g.edges = kCsrChunk;
     g.ndesc = t->cap_desc;
     g.grid = cfg.grid;
     for (int b = 0; b < 2; ++b) {

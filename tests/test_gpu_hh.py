@@ -298,3 +298,60 @@ def test_hh_banded_graph_on_a_small_grid(nd, n, prec):
     if prec == 0:
         ref, _, _ = O.run(O.csr(n, rp, col, w, HH_PRM, iapp), y0, 0.01, 5)
         assert normwise(got[0], ref) < 1e-12
+
+
+def graph_nodes(torch, g):
+    """Number of nodes of a captured (kept) graph."""
+    import ctypes
+    import os
+    hip = ctypes.CDLL(os.path.join(os.path.dirname(torch.__file__), "lib", "libamdhip64.so"))
+    n = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_hh_networks_of_all_degrees_and_sizes_share_launches(nd, prec):
+    """A batch of networks with every default of edges per thread and both row
+    counts per work item takes as many launches as one of equal networks, and gives
+    each network the bits of its run alone; so does an explicit value beside others."""
+    import torch
+    steps = 4
+    cases = [(700, 5), (66000, 40), (3000, 100), (1500, 60)]
+    st = torch.cuda.Stream()
+    nodes = {}
+    for kind in ("equal", "mixed"):
+        shapes = cases if kind == "mixed" else [cases[0]] * len(cases)
+        hs, y0s, alone = [], [], []
+        try:
+            for n, deg in shapes:
+                rp, col, w = inputs.random_out_graph(deg, n, deg)
+                y0s.append(torch.from_numpy(inputs.hh_state(3, n)).cuda())
+                hs.append(nd.nd_create(nd.problem(nd.ND_HH, nd.ND_CSR, n, HH_PRM, precision=prec, row_ptr=rp, col=col,
+                                                  weight=w, per_elem=inputs.hh_iapp(3, n))))
+            c = nd.nd_get_config(hs[-1])
+            c.tile_y = 2
+            nd.nd_set_config(hs[-1], c)
+            print(f"case hh shared launches {kind} prec={prec}", flush=True)
+            with torch.cuda.stream(st):
+                for h, y0 in zip(hs, y0s):
+                    nd.nd_set_state(h, y0, stream=st)
+                    nd.nd_run(h, 0.01, steps, stream=st)
+                    alone.append(torch.empty_like(y0))
+                    nd.nd_get_state(h, alone[-1], stream=st)
+                    nd.nd_set_state(h, y0, stream=st)
+                nd.nd_run_batch_noalloc(hs, [0.01] * len(hs), [steps] * len(hs), stream=st)
+                for h, y in zip(hs, alone):
+                    got = torch.empty_like(y)
+                    nd.nd_get_state(h, got, stream=st)
+                    nd.nd_sync(h, stream=st)
+                    assert torch.equal(got, y)
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph(keep_graph=True)
+            with torch.cuda.graph(g, stream=st):
+                nd.nd_run_batch_noalloc(hs, [0.01] * len(hs), [steps] * len(hs), stream=st)
+            nodes[kind] = graph_nodes(torch, g)
+        finally:
+            for h in hs:
+                nd.nd_destroy(h)
+    assert nodes["equal"] == nodes["mixed"], nodes
