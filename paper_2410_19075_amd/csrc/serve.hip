@@ -6,12 +6,12 @@
 // left, and retires the requests whose last chunk has completed.  Admitted
 // requests are grouped by kernel class (model, topology, precision, tile
 // shape); every class owns a fixed-capacity descriptor table and work map in
-// device memory and one chunk graph captured once with a persistent grid.
-// Between chunks only the table contents change (double-buffered pinned host
-// staging, async copies on the pump's stream), so the same graph is replayed
-// whatever the mix of requests.  A request's kernels and tile decomposition
-// depend on its own problem only, so its arithmetic is identical alone and in
-// any mix.
+// device memory and a chunk graph captured once with a persistent grid (CSR: once
+// per launch shape its requests need).  Between chunks only the table contents
+// change (double-buffered pinned host staging, async copies), so the same graph
+// is replayed whatever the mix of requests.  A request's tile decomposition
+// depends on its own problem only and its sums on nothing else, so its
+// arithmetic is identical alone and in any mix.
 //
 // The device is kept busy across pumps: a pump enqueues chunk k+1 before it
 // waits for chunk k, so admission, retirement and the host's table updates run
@@ -34,6 +34,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -41,7 +42,6 @@
 #include <map>
 #include <memory>
 #include <mutex>
-#include <tuple>
 #include <vector>
 
 #include "runtime.h"
@@ -54,13 +54,9 @@ namespace nd {
         if (e_ != hipSuccess) return hip_fail(e_, #expr); \
     } while (0)
 
-using ClassKey = std::tuple<int, int, int, int, int, int, int>;
-
-static ClassKey class_key(const Net* n) {
-    if (n->prob.topo == ND_CSR)
-        return ClassKey(n->prob.model, n->prob.topo, n->prob.precision, 0, n->cfg.tile_y, 0, csr_rows(n->prob.n));
-    return std::tuple_cat(n->kernel_class());
-}
+// What a captured chunk depends on besides the class and its tables: mean-velocity
+// kernels; CSR: edges in flight, whether they differ, workgroup size, LDS.
+using ChunkShape = std::array<int, 5>;
 
 struct Request {
     nd_req id = 0;
@@ -86,8 +82,8 @@ struct Request {
 };
 
 struct ClassTable {
-    ClassKey key;
-    Group g{};
+    Net::Class key;
+    Group g;  // of the chunk being enqueued
     int cap_desc = 0, cap_work = 0;
     void* dev = nullptr;  // desc | work | nwork
     // host staging, double-buffered by chunk parity: the copies of chunk k read
@@ -95,12 +91,34 @@ struct ClassTable {
     NetDesc* h_desc[2] = {nullptr, nullptr};
     int2* h_work[2] = {nullptr, nullptr};
     int* h_nwork[2] = {nullptr, nullptr};
-    hipGraphExec_t exec[2] = {nullptr, nullptr};  // without / with mean-velocity kernels
+    std::map<ChunkShape, hipGraphExec_t> exec;  // captured chunks (at most kMaxExec)
+    static constexpr size_t kMaxExec = 16;
     std::vector<Request*> slots;
 
+    // Start the group of a chunk, without networks.
+    void reset_group() {
+        Group n(key);
+        n.ndesc = g.ndesc;
+        n.grid = g.grid;
+        n.desc = g.desc;
+        n.work = g.work;
+        n.nwork = g.nwork;
+        g = n;
+    }
+    // CSR: the LDS of the chunk's own networks, rounded up so that a few captured chunks
+    // serve all (320 steps of eight networks of 7000 neurons, degree 10 / 100: 14 / 29 ms;
+    // with the LDS of the largest possible chunk 19 / 36 ms, two workgroups a CU).
+    void round_group() {
+        if (g.topo == ND_CSR) g.edges = std::min(kCsrChunk, (g.edges + 511) / 512 * 512);
+    }
+    ChunkShape shape() const { return {g.mv, g.tile_y, g.mixed, g.block, g.edges}; }
+    void drop_exec() {  // no chunk may be in flight
+        for (auto& e : exec) (void)hipGraphExecDestroy(e.second);
+        exec.clear();
+    }
+
     ~ClassTable() {
-        for (auto& e : exec)
-            if (e) (void)hipGraphExecDestroy(e);
+        drop_exec();
         if (dev) (void)hipFree(dev);
         for (int b = 0; b < 2; ++b) {
             if (h_desc[b]) (void)hipHostFree(h_desc[b]);
@@ -224,11 +242,7 @@ nd_status Server::grow_work(ClassTable* t, int need) {
     nd_status s = drain();
     if (s) return s;
     int cap = std::max(need, std::max(1024, 2 * t->cap_work));
-    for (auto& e : t->exec)
-        if (e) {
-            (void)hipGraphExecDestroy(e);
-            e = nullptr;
-        }
+    t->drop_exec();
     if (t->dev) (void)hipFree(t->dev);
     t->dev = nullptr;
     for (int b = 0; b < 2; ++b) {
@@ -246,7 +260,7 @@ nd_status Server::grow_work(ClassTable* t, int need) {
 }
 
 nd_status Server::table_for(Request* r, ClassTable** out) {
-    const ClassKey key = class_key(r->net);
+    const Net::Class key = r->net->kernel_class();
     for (auto& t : classes)
         if (t->key == key) {
             *out = t.get();
@@ -256,17 +270,9 @@ nd_status Server::table_for(Request* r, ClassTable** out) {
     t->key = key;
     t->cap_desc = cfg.max_slots;
     t->slots.assign(cfg.max_slots, nullptr);
-    Group& g = t->g;
-    g.model = std::get<0>(key);
-    g.topo = std::get<1>(key);
-    g.prec = std::get<2>(key);
-    g.tile = std::get<3>(key);
-    g.tile_y = std::get<4>(key);
-    g.h = std::get<5>(key);
-    g.block = std::get<6>(key);
-    g.edges = kCsrChunk;
-    g.ndesc = t->cap_desc;
-    g.grid = cfg.grid;
+    t->g = Group(key);
+    t->g.ndesc = t->cap_desc;
+    t->g.grid = cfg.grid;
     for (int b = 0; b < 2; ++b) {
         HIPC(hipHostMalloc((void**)&t->h_desc[b], (size_t)t->cap_desc * sizeof(NetDesc)));
         HIPC(hipHostMalloc((void**)&t->h_nwork[b], 64));
@@ -372,10 +378,14 @@ nd_status Server::launch_class(ClassTable* t, int b, hipStream_t on) {
     HIPC(hipMemcpyAsync(t->g.work, t->h_work[b], (size_t)std::max(w, 1) * sizeof(int2), hipMemcpyHostToDevice, on));
     HIPC(hipMemcpyAsync(t->g.nwork, t->h_nwork[b], sizeof(int), hipMemcpyHostToDevice, on));
     if (!graphs_enabled()) return enqueue_chunk(t->g, K, on);
-    hipGraphExec_t& ex = t->exec[t->g.mv ? 1 : 0];
-    nd_status s;
-    if (!ex && (s = capture_chunk(t->g, K, &ex))) return s;
-    HIPC(hipGraphLaunch(ex, on));
+    auto ex = t->exec.find(t->shape());
+    if (ex == t->exec.end()) {
+        hipGraphExec_t e;
+        const nd_status s = capture_chunk(t->g, K, &e);
+        if (s) return s;
+        ex = t->exec.emplace(t->shape(), e).first;
+    }
+    HIPC(hipGraphLaunch(ex->second, on));
     return ND_OK;
 }
 
@@ -394,17 +404,22 @@ nd_status Server::launch(hipStream_t strm, bool* launched) {
         ClassTable* t = tp.get();
         int nw = 0;
         int64_t values = 0;
-        bool mv = false, any = false;
+        bool any = false;
+        t->reset_group();
         for (Request* r : t->slots)
             if (r && r->in_chunk) {
                 any = true;
                 nw += (int)r->net->work_items();
                 values += r->net->prob.n * nvars_of(r->net->prob.model);
-                mv = mv || r->net->mv_start >= 0;
+                t->g.take(*r->net);
             }
         if (!any) continue;
+        t->round_group();
         if ((s = grow_work(t, nw))) return s;  // (waits for the chunks in flight before it replaces a table)
-        t->g.mv = mv;
+        if (t->exec.size() >= ClassTable::kMaxExec && !t->exec.count(t->shape())) {
+            if ((s = drain())) return s;
+            t->drop_exec();
+        }
         act.emplace_back(class_cost(t->g, nw, values), t);
     }
     if (act.empty()) return ND_OK;

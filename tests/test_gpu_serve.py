@@ -141,3 +141,30 @@ def test_cancel_running_request_frees_its_slot(nd):
         assert nd.nd_server_stats(s).bytes_in_use == 0
     finally:
         nd.nd_server_destroy(s)
+
+
+@pytest.mark.parametrize("grid", [0, 64])
+def test_hh_requests_of_all_degrees_and_sizes(nd, grid):
+    """HH requests join and leave one class while its chunks change shape (edges in
+    flight, rows per work item, LDS): every result has the bits of its run alone."""
+    shapes = [(3000, 5, 60), (700, 100, 25), (66000, 20, 40), (2500, 60, 30), (1500, 10, 90)]
+    cs = []
+    for n, deg, steps in shapes:
+        rp, col, w = inputs.random_out_graph(deg, n, deg)
+        cs.append((nd.problem(nd.ND_HH, nd.ND_CSR, n, HH_PRM, row_ptr=rp, col=col, weight=w,
+                              per_elem=inputs.hh_iapp(9, n)), inputs.hh_state(9, n), steps))
+    alone = [nd.simulate(p, y0, 0.01, steps)[0] for p, y0, steps in cs]
+    print(f"case serve hh mix grid={grid}", flush=True)
+    s = nd.nd_server_create(8 << 30, max_slots=3, chunk_steps=8, grid=grid)
+    try:
+        ids = []
+        for p, y0, steps in cs:
+            ids.append(nd.nd_server_submit(s, p, y0, 0.01, steps))
+            nd.nd_server_pump(s)
+        drain(nd, s)
+        for rid, ya, (_, y0, _) in zip(ids, alone, cs):
+            y = np.empty_like(y0)
+            nd.nd_server_result(s, rid, y)
+            assert np.array_equal(y, ya)
+    finally:
+        nd.nd_server_destroy(s)
