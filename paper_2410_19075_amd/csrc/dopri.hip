@@ -23,6 +23,7 @@
 #include <cmath>
 
 #include "models.h"
+#include "carve.h"
 #include "runtime.h"
 
 namespace nd {
@@ -832,33 +833,48 @@ static nd_status run_adaptive_tiled(const std::vector<Net*>& nets, int model, in
     std::vector<DtCtl> cs(count);
     std::vector<NetDesc> descs(count);
     std::vector<int2> work;
-    size_t bytes = 0;
     for (int b = 0; b < count; ++b) {
-        const Net* nt = nets[b];
-        const int64_t n = nt->prob.n, len = nvars_of(nt->prob.model) * n, G = (n + T - 1) / T;
-        bytes += (size_t)(9 * len + 4 * n + 5 * G) * 8 + sizeof(DtCtl);
-        if (dense) bytes += (size_t)(2 * ((int64_t)std::floor(t_end[b] / t_out) + 1) * G) * 8;
+        const int64_t G = (nets[b]->prob.n + T - 1) / T;
         for (int64_t t = 0; t < G; ++t) work.push_back(make_int2(b, (int)t));
     }
     const size_t bd = (size_t)count * sizeof(DtNet), bn = (size_t)count * sizeof(NetDesc),
                  bw = work.size() * sizeof(int2);
     const size_t br = dense ? (size_t)count * r_stride * 8 : 0, by = dense && Yh ? (size_t)count * y_stride * 8 : 0;
-    bytes += br + by;
-    char* buf = nullptr;
-    hipError_t e = hipMallocAsync((void**)&buf, bd + bn + bw + bytes + 256, st);
-    if (e != hipSuccess) return hip_fail(e, "adaptive scratch");
-    DtNet* d_r = (DtNet*)buf;
-    NetDesc* d_desc = (NetDesc*)(buf + bd);
-    int2* d_work = (int2*)(buf + bd + bn);
-    char* p = buf + ((bd + bn + bw + 255) / 256) * 256;
-    auto take = [&](size_t nbytes) {
-        char* q = p;
-        p += (nbytes + 7) / 8 * 8;
-        return q;
+    DtNet* d_r = nullptr;
+    NetDesc* d_desc = nullptr;
+    int2* d_work = nullptr;
+    double* d_out = nullptr;  // dense output: R, then the states
+    auto lay = [&](Carve c) {
+        d_r = c.take<DtNet>(count);
+        d_desc = c.take<NetDesc>(count);
+        d_work = c.take<int2>(work.size());
+        for (int b = 0; b < count; ++b) {
+            const int64_t n = nets[b]->prob.n, len = nvars_of(nets[b]->prob.model) * n, G = (n + T - 1) / T;
+            DtNet& r = rs[b];
+            r.y[1] = c.take<double>(len);
+            for (int q = 0; q < 7; ++q) r.k[q] = c.take<double>(len);
+            r.Z = c.take<double>(len);
+            for (int b2 = 0; b2 < 2; ++b2) {  // a network needs the maps or the prefix sums
+                double* q = c.take<double>(2 * n);
+                r.M[b2] = topo == ND_LINKS ? q : nullptr;
+                r.pre[b2] = topo == ND_LINKS ? nullptr : q;
+                r.tot[b2] = c.take<double>(2 * G);
+            }
+            r.errp = c.take<double>(G);
+            r.ctl = c.take<DtCtl>(1);
+            r.K = dense ? (int64_t)std::floor(t_end[b] / t_out) : -1;
+            r.Rpart = dense ? c.take<double>(2 * (r.K + 1) * G) : nullptr;
+        }
+        d_out = c.take<double>((br + by) / 8);
+        return c.bytes();
     };
+    char* buf = nullptr;
+    hipError_t e = hipMallocAsync((void**)&buf, lay(Carve()), st);
+    if (e != hipSuccess) return hip_fail(e, "adaptive scratch");
+    lay(Carve(buf));
     for (int b = 0; b < count; ++b) {
         const Net* nt = nets[b];
-        const int64_t n = nt->prob.n, len = nvars_of(nt->prob.model) * n;
+        const int64_t n = nt->prob.n;
         DtNet& r = rs[b];
         r.n = (int32_t)n;
         r.P = (int32_t)nt->prob.radius;
@@ -867,19 +883,6 @@ static nd_status run_adaptive_tiled(const std::vector<Net*>& nets, int model, in
         r.tend = t_end[b];
         descs[b] = nt->run_desc(dt0[b], 0);
         r.y[0] = descs[b].y[descs[b].ypar];
-        r.y[1] = (double*)take(len * 8);
-        for (int q = 0; q < 7; ++q) r.k[q] = (double*)take(len * 8);
-        r.Z = (double*)take(len * 8);
-        for (int b2 = 0; b2 < 2; ++b2) {  // a network needs the maps or the prefix sums
-            double* q = (double*)take(2 * n * 8);
-            r.M[b2] = topo == ND_LINKS ? q : nullptr;
-            r.pre[b2] = topo == ND_LINKS ? nullptr : q;
-            r.tot[b2] = (double*)take(2 * r.G * 8);
-        }
-        r.errp = (double*)take(r.G * 8);
-        r.ctl = (DtCtl*)take(sizeof(DtCtl));
-        r.K = dense ? (int64_t)std::floor(t_end[b] / t_out) : -1;
-        r.Rpart = dense ? (double*)take(2 * (r.K + 1) * r.G * 8) : nullptr;
         r.R = nullptr;
         r.Y = nullptr;
         DtCtl& c = cs[b];
@@ -900,8 +903,8 @@ static nd_status run_adaptive_tiled(const std::vector<Net*>& nets, int model, in
             c.hs_prev = 1.0;
         }
     }
-    double* d_R = dense ? (double*)take(br) : nullptr;
-    double* d_Y = by ? (double*)take(by) : nullptr;
+    double* d_R = dense ? d_out : nullptr;
+    double* d_Y = by ? d_out + br / 8 : nullptr;
     for (int b = 0; b < count; ++b) {
         if (d_R) rs[b].R = d_R + (size_t)b * r_stride;
         if (d_Y) rs[b].Y = d_Y + (size_t)b * y_stride;

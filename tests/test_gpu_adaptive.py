@@ -392,3 +392,38 @@ def test_adaptive_links_at_tile_edges(nd, model, n):
         nd.nd_destroy(h)
     assert (std.accepted, std.rejected) == (acc, rej)
     assert normwise(Y[0].reshape(5, nv * n)[4], ref, nv) < 1e-10
+
+
+def test_tiled_adaptive_batch_of_odd_matrices_equals_each_alone(nd):
+    """Matrix networks of one variable and odd sizes in one batch: their maps are read
+    in pairs of doubles behind pieces of odd lengths; the bits of each run alone."""
+    cases = []
+    for n, P in ((301, 5), (777, 9), (1025, 3)):
+        rp, col = inputs.small_world_links(n, n, P, 20)
+        cases.append((nd.problem(nd.ND_KURAMOTO, nd.ND_LINKS, n, [0.0, 1.0, 1.3], row_ptr=rp, col=col),
+                      inputs.kuramoto_phases(n, n)))
+
+    def run(which):
+        hs = [nd.nd_create(cases[i][0]) for i in which]
+        try:
+            for h, i in zip(hs, which):
+                nd.nd_set_state(h, cases[i][1], on_device=0)
+            _, R, Y = nd.nd_run_adaptive_dense(hs, [3.0] * len(hs), [0.01] * len(hs), 1e-7, 1e-9, 0.7,
+                                               state_len=1025)
+            out = []
+            for h, i in zip(hs, which):
+                y = np.empty_like(cases[i][1])
+                nd.nd_get_state(h, y, on_device=0)
+                out.append(y)
+            return out, R, [y[:5 * len(cases[i][1])] for y, i in zip(Y, which)]
+        finally:
+            for h in hs:
+                nd.nd_destroy(h)
+
+    print("case adaptive odd matrices", flush=True)
+    batch, Rb, Yb = run([0, 1, 2])
+    for i in range(3):
+        alone, Ra, Ya = run([i])
+        assert np.array_equal(batch[i], alone[0])
+        assert np.array_equal(Rb[i], Ra[0])
+        assert np.array_equal(Yb[i], Ya[0])
