@@ -218,14 +218,20 @@ nd_status nd_destroy(nd_handle h);
 typedef struct nd_kernel_config {
     int32_t tile;   /* ring: elements per tile (128, 256, 512, 1024 or 2048), or -1024 / -2048 / -4096:
                        the whole ring (n <= that capacity) resident in one workgroup;
-                       cube: output tile extent along x; CSR: rows per workgroup */
+                       cube: output tile extent along x; CSR: rows per work item, fixed by the size
+                       (256, from 65536 neurons 512; nd_set_config takes 256 for either) */
     int32_t block;  /* threads per workgroup: derived (ignored by nd_set_config), except for
-                       ND_BALL3D / ND_DISK2D, where it selects 256 or 1024 */
+                       ND_BALL3D / ND_DISK2D, where it selects 256 or 1024 (CSR networks of 256
+                       rows that share a batch with some of 512 run in workgroups of 512) */
     int32_t grid;   /* persistent grid size in workgroups; 0 = one workgroup per work item */
-    int32_t chunk;  /* steps per captured graph chunk */
+    int32_t chunk;  /* steps per captured graph chunk (rings resident in one workgroup have no such
+                       graph: nd_run and nd_run_batch give them up to 1024 steps per launch
+                       whatever this says; the server's chunks are nd_server_config's) */
     int32_t tile_y; /* cube: output tile extent along y ((tile+2h)*(tile_y+2h) <= 1024);
-                       CSR: edges each thread streams per chunk (2, 4, 8 or 16; results
-                       do not depend on it) */
+                       CSR: edges each thread has in flight (2, 4, 8 or 16; results do not
+                       depend on it; networks that share launches in a batch or on the
+                       server take one value, that of the network with the most links, at
+                       most 8 if the values differ and all have 256 rows) */
     int32_t tile_z; /* cube: planes per work item */
 } nd_kernel_config;
 

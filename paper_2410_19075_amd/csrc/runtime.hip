@@ -411,13 +411,12 @@ nd_kernel_config default_config(const nd_problem* p) {
         c.tile = kLinksRows;  // rows per work item
         c.block = 256;
     } else {
-        c.tile = 256;
+        c.tile = c.block = csr_rows(p->n);
         // edges per thread in flight: as many as the mean (512-row tile, source block)
         // half fills.  2e5 neurons, us per stage with 4 / 8 / 16 (FP64): degree 100
         // 88 / 81 / 73, degree 10 27 / 29 / 34 (more registers, fewer waves)
         const int64_t edges = p->nnz / kCsrSourceBlocks * 512 / p->n;
         c.tile_y = edges > 8 * 512 ? 16 : edges > 4 * 512 ? 8 : 4;
-        c.block = 256;
     }
     return c;
 }
@@ -821,8 +820,7 @@ nd_status Net::apply_config(const nd_kernel_config& c) {
         tmpl.tile = kLinksRows;
         tmpl.G = (int32_t)((n + kLinksRows - 1) / kLinksRows);
     } else {
-        cfg.block = 256;
-        cfg.tile = 256;  // the one accepted value (the kernels take csr_rows(n) rows per work item)
+        cfg.tile = cfg.block = csr_rows(n);  // rows per work item (fixed by the layout of the edges)
         tmpl.tile = csr_rows(n);
         tmpl.G = (int32_t)(kCsrSourceBlocks * ((n + csr_rows(n) - 1) / csr_rows(n)));  // (row tile, source block)
     }
@@ -1652,7 +1650,10 @@ nd_status nd_set_config(nd_handle h, const nd_kernel_config* cfg) {
         if (c.tile != kLinksRows) return fail(ND_ERR_INVALID_ARG, "links work items hold %d rows (tile must be %d)",
                                               kLinksRows, kLinksRows);
     } else {
-        if (c.tile != 256) return fail(ND_ERR_INVALID_ARG, "CSR work items hold 256 rows (tile must be 256)");
+        // 256 for every size too: configurations written when all networks had 256 rows
+        if (c.tile != 256 && c.tile != csr_rows(p.n))
+            return fail(ND_ERR_INVALID_ARG, "CSR work items of this network hold %d rows (tile must be %d or 256)",
+                        csr_rows(p.n), csr_rows(p.n));
         if (c.tile_y < 2 || c.tile_y > 16 || (c.tile_y & (c.tile_y - 1)))
             return fail(ND_ERR_INVALID_ARG, "CSR edges per thread must be 2, 4, 8 or 16");
     }

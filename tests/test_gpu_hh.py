@@ -355,3 +355,33 @@ def test_hh_networks_of_all_degrees_and_sizes_share_launches(nd, prec):
             for h in hs:
                 nd.nd_destroy(h)
     assert nodes["equal"] == nodes["mixed"], nodes
+
+
+@pytest.mark.parametrize("n, rows", [(65535, 256), (65536, 512)])
+def test_hh_config_reports_the_rows_that_run(nd, n, rows):
+    """nd_get_config gives the rows per work item of the size; set back, or with the
+    256 that configurations of every size held before, it is accepted and changes
+    nothing, other values are refused."""
+    g = inputs.random_out_graph(8, n, 4)
+    y, p, y0, _ = run_net(nd, n, g, 2)
+    h = nd.nd_create(p)
+    try:
+        c = nd.nd_get_config(h)
+        assert (c.tile, c.block) == (rows, rows)
+        for tile in (rows, 256):
+            print(f"case hh config n={n} tile={tile}", flush=True)
+            c.tile = tile
+            nd.nd_set_config(h, c)
+            c = nd.nd_get_config(h)
+            assert (c.tile, c.block) == (rows, rows)
+            nd.nd_set_state(h, y0, on_device=0)
+            nd.nd_run(h, 0.01, 2)
+            got = np.empty_like(y)
+            nd.nd_get_state(h, got, on_device=0)
+            assert np.array_equal(got, y)
+        for tile in (0, 128, 2 * rows):
+            c.tile = tile
+            with pytest.raises(nd.NDError):
+                nd.nd_set_config(h, c)
+    finally:
+        nd.nd_destroy(h)
