@@ -372,9 +372,9 @@ def roofline(wl, args, prec, ev_total, cfg):
     taken on the current kernel sources (else null)."""
     from paper_2410_19075_amd import profsum
     if args.workload == "kuramoto" and cfg["tile"] < 0:
-        # rings resident in one workgroup for up to 1024 steps a launch: no HBM
-        # traffic between stages, so the bound is the FP64 ALU rate
-        launches = args.steps * -(-args.horizon // 1024)
+        # rings resident in one workgroup for up to 1024 steps a launch (fewer beyond
+        # 2^22 elements): no HBM traffic between stages, so the bound is the FP64 ALU rate
+        launches = args.steps * -(-args.horizon // min(1024, max(64, (1 << 32) // (args.batch * wl.n))))
         flops = args.batch * wl.n * args.horizon * args.steps * KURAMOTO_RESIDENT_FLOPS
         achieved = flops / ev_total / 1e12
         return {"bound": "alu", "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",

@@ -225,8 +225,9 @@ typedef struct nd_kernel_config {
                        rows that share a batch with some of 512 run in workgroups of 512) */
     int32_t grid;   /* persistent grid size in workgroups; 0 = one workgroup per work item */
     int32_t chunk;  /* steps per captured graph chunk (rings resident in one workgroup have no such
-                       graph: nd_run and nd_run_batch give them up to 1024 steps per launch
-                       whatever this says; the server's chunks are nd_server_config's) */
+                       graph: nd_run and nd_run_batch give them up to 1024 steps per launch,
+                       fewer beyond 4 10^6 elements, whatever this says; the server's
+                       chunks are nd_server_config's) */
     int32_t tile_y; /* cube: output tile extent along y ((tile+2h)*(tile_y+2h) <= 1024);
                        CSR: edges each thread has in flight (2, 4, 8 or 16; results do not
                        depend on it; networks that share launches in a batch or on the

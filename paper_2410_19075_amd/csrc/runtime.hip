@@ -1064,13 +1064,19 @@ constexpr int64_t kEagerValues = int64_t(1) << 20;
 // Steps per launch of rings resident in one workgroup.  A chunk is one kernel
 // there, so replaying captured 64-step chunks only added launches (and a capture
 // per batch): 0.97 us per stage of one 1024-ring in replays, 0.93 us in one launch;
-// 512 rings 1.77 and 1.67 us.  The limit keeps a launch to some tens of milliseconds.
-constexpr int64_t kResidentSteps = 1024;
+// 512 rings 1.77 and 1.67 us.  Beyond 4 10^6 elements, where a step of the batch takes
+// 36 us (4096 Kuramoto rings of 1024, FP64) and more rings take as much longer, the
+// steps are cut so that a launch stays at some tens of milliseconds; 64 steps at the
+// least, whose launch costs nothing beside them.
+static int64_t resident_steps(int64_t elements) {
+    return std::clamp((int64_t(1) << 32) / elements, int64_t(64), int64_t(1024));
+}
 
-// A group of resident rings: chunks of kResidentSteps launched directly.
-static nd_status run_resident(const Group& g, int64_t maxsteps, hipStream_t st) {
-    for (int64_t done = 0; done < maxsteps; done += kResidentSteps) {
-        const nd_status s = enqueue_chunk(g, (int)std::min(kResidentSteps, maxsteps - done), st);
+// A group of resident rings of so many elements: chunks launched directly.
+static nd_status run_resident(const Group& g, int64_t elements, int64_t maxsteps, hipStream_t st) {
+    const int64_t K = resident_steps(elements);
+    for (int64_t done = 0; done < maxsteps; done += K) {
+        const nd_status s = enqueue_chunk(g, (int)std::min(K, maxsteps - done), st);
         if (s) return s;
     }
     return ND_OK;
@@ -1267,7 +1273,7 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
         for (int q : idx) values += nets[q]->prob.n * nvars_of(nets[q]->prob.model);
         const bool eager = values >= kEagerValues;
         if (g.topo == ND_RING && g.tile < 0) {
-            if ((s = run_resident(g, maxsteps, st))) return s;
+            if ((s = run_resident(g, values / nvars_of(g.model), maxsteps, st))) return s;
         } else if (maxsteps <= K || !graphs_enabled() || eager) {
             // one eager chunk covering every network's steps
             if ((s = enqueue_chunk(g, (int)std::min<int64_t>(maxsteps, 1 << 30), st))) return s;
@@ -1443,7 +1449,7 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
         const int K = std::max(1, n0->cfg.chunk);
         const bool eager = values >= kEagerValues;
         if (g.topo == ND_RING && g.tile < 0) {
-            if ((s = run_resident(g, maxsteps, st))) return s;
+            if ((s = run_resident(g, values / nvars_of(g.model), maxsteps, st))) return s;
         } else if (maxsteps <= K || !graphs_enabled() || eager) {
             if ((s = enqueue_chunk(g, (int)std::min<int64_t>(maxsteps, 1 << 30), st))) return s;
         } else {

@@ -350,3 +350,42 @@ def test_kuramoto_phase_shift_invariance_large_phases(nd, tile):
     ref, _, _ = O.run(O.ring(O.KURAMOTO, n, P, prm), y0, 0.01, 50)
     # the shifted state carries ~1e-10 rounding per step in y itself
     assert np.max(np.abs((y - shift) - ref)) < 2e-8
+
+
+def test_resident_batch_beyond_one_launch_per_1024_steps(nd):
+    """A batch of resident rings whose elements limit a launch to fewer than 1024
+    steps: rings from both ends of the batch, R recorded across the launches and
+    a horizon that ends inside the second one, have the bits of their runs alone."""
+    import torch
+    n, P, count, steps = 4096, 1000, 1100, 1000  # 953 steps a launch
+    p = nd.problem(nd.ND_KURAMOTO, nd.ND_RING, n, [0.0, 1.0, 1.46], radius=P)
+    y0 = torch.from_numpy(inputs.kuramoto_phases(8, n)).cuda()
+    y1 = torch.from_numpy(inputs.kuramoto_phases(9, n)).cuda()
+    obs = nd.observe(7, -1)
+    hs = [nd.nd_create(p) for _ in range(count)]
+    print(f"case resident batch {count} x {n}", flush=True)
+    try:
+        for i, h in enumerate(hs):
+            nd.nd_set_state(h, y1 if i == count - 1 else y0)
+        nd.nd_run_batch(hs, [0.01] * count, [steps] * (count - 1) + [steps - 20],
+                        [obs if i in (0, count - 1) else nd.observe(0, -1) for i in range(count)])
+        got = []
+        for h, s in ((hs[0], steps), (hs[1], steps), (hs[-1], steps - 20)):
+            y, R = torch.empty_like(y0), torch.empty(s // 7 + 1, dtype=torch.float64, device="cuda")
+            nd.nd_get_state(h, y)
+            if h != hs[1]:
+                nd.nd_get_observables(h, R=R)
+            nd.nd_sync(h)
+            got.append((y, R))
+        for h, y, s, (yb, Rb) in ((hs[0], y0, steps, got[0]), (hs[2], y1, steps - 20, got[2])):
+            nd.nd_set_state(h, y)
+            nd.nd_run(h, 0.01, s, obs)
+            ya, Ra = torch.empty_like(y0), torch.empty(s // 7 + 1, dtype=torch.float64, device="cuda")
+            nd.nd_get_state(h, ya)
+            nd.nd_get_observables(h, R=Ra)
+            nd.nd_sync(h)
+            assert torch.equal(ya, yb) and torch.equal(Ra, Rb)
+        assert torch.equal(got[0][0], got[1][0])
+    finally:
+        for h in hs:
+            nd.nd_destroy(h)
