@@ -87,6 +87,8 @@ struct Net {
     nd_status alloc(void** ptr, size_t bytes);
     void free_buf(void* ptr);
     nd_status create(const nd_problem* p);
+    template <class KT>
+    nd_status upload_edges(const nd_problem* p);
     nd_status apply_config(const nd_kernel_config& c);
     int64_t work_items() const;
     // Networks of one kernel class share launches: model, topology, precision, tile,

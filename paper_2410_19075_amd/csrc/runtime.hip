@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "nd_dev.h"
+#include "csr_layout.h"
 #include "runtime.h"
 
 namespace nd {
@@ -618,47 +619,23 @@ static void derive_params(const nd_problem* p, NetDesc& d) {
     }
 }
 
-// Sort the edges of every chunk (the kCsrChunk-edge pieces of a row tile's edges
-// of one source block) by source and pack each with its place in row order; the
-// weights follow.  Two counting passes over the source's bits per chunk.
-static void csr_sort_chunks(int64_t n, const std::vector<int64_t>& bptr, std::vector<uint32_t>& col,
-                            std::vector<double>& w) {
-    constexpr int kBits = 10, kBuckets = 1 << kBits;
-    const int64_t rows = csr_rows(n);
-    static_assert(32 - kCsrSlotBits <= 2 * kBits, "two passes cover the source bits");
-    std::vector<uint32_t> a(kCsrChunk), t(kCsrChunk);
-    std::vector<double> wr(kCsrChunk);
-    std::vector<int> cnt[2] = {std::vector<int>(kBuckets), std::vector<int>(kBuckets)};
-    for (int b = 0; b < kCsrSourceBlocks; ++b) {
-        const int64_t* p = bptr.data() + (size_t)b * (n + 1);
-        const uint32_t base = (uint32_t)csr_block_begin(b, n);
-        for (int64_t r0 = 0; r0 < n; r0 += rows) {
-            const int64_t e1 = p[std::min(r0 + rows, n)];
-            for (int64_t c0 = p[r0]; c0 < e1; c0 += kCsrChunk) {
-                const int m = (int)std::min<int64_t>(kCsrChunk, e1 - c0);
-                for (auto& c : cnt) std::fill(c.begin(), c.end(), 0);
-                for (int q = 0; q < m; ++q) {
-                    const uint32_t v = col[c0 + q] - base;
-                    a[q] = v << kCsrSlotBits | (uint32_t)q;
-                    ++cnt[0][v & (kBuckets - 1)];
-                    ++cnt[1][v >> kBits];
-                }
-                for (auto& c : cnt)
-                    for (int o = 0, i = 0; i < kBuckets; ++i) {
-                        const int k = c[i];
-                        c[i] = o;
-                        o += k;
-                    }
-                for (int q = 0; q < m; ++q) t[cnt[0][a[q] >> kCsrSlotBits & (kBuckets - 1)]++] = a[q];
-                for (int q = 0; q < m; ++q) a[cnt[1][t[q] >> (kCsrSlotBits + kBits)]++] = t[q];
-                std::copy(w.begin() + c0, w.begin() + c0 + m, wr.begin());
-                for (int q = 0; q < m; ++q) {
-                    col[c0 + q] = a[q];
-                    w[c0 + q] = wr[a[q] & (kCsrChunk - 1)];
-                }
-            }
-        }
+// Upload a CSR network's edges in the gather kernel's layout.
+template <class KT>
+nd_status Net::upload_edges(const nd_problem* pr) {
+    const int64_t nnz = pr->nnz;
+    const CsrLayout<KT> L = csr_layout<KT>(pr->n, pr->row_ptr, pr->col, pr->weight);
+    csr_edges = L.edges;
+    NetDesc& d = tmpl;
+    nd_status s;
+    if ((s = alloc((void**)&d.row_ptr, L.bptr.size() * 8))) return s;
+    if ((s = alloc((void**)&d.col, std::max<int64_t>(nnz, 1) * 4))) return s;
+    if ((s = alloc((void**)&d.w, std::max<int64_t>(nnz, 1) * sizeof(KT)))) return s;
+    HIPC(setup_copy(astream, (void*)d.row_ptr, L.bptr.data(), L.bptr.size() * 8));
+    if (nnz > 0) {
+        HIPC(setup_copy(astream, (void*)d.col, L.col.get(), nnz * 4));
+        HIPC(setup_copy(astream, (void*)d.w, L.w.get(), nnz * sizeof(KT)));
     }
+    return ND_OK;
 }
 
 nd_status Net::create(const nd_problem* pr) {
@@ -687,68 +664,11 @@ nd_status Net::create(const nd_problem* pr) {
     for (int b = 0; b < 3; ++b)
         if ((s = alloc(&d.k[b], V * n * kb))) return s;
     if (pr->topo == ND_CSR) {
-        // split every row's in-edges by source block (sources ascending, so each
-        // block keeps its order) and lay the blocks out one after the other
-        constexpr int B = kCsrSourceBlocks;
-        const int64_t nnz = pr->nnz;
-        std::vector<int64_t> bptr((size_t)B * (n + 1), 0);
-        int64_t begin[B + 1];  // first source of each block
-        for (int b = 0; b <= B; ++b) begin[b] = csr_block_begin(b, n);
-        // block of a source, starting from the block of the row's last one (sources
-        // usually ascend: no division per edge)
-        auto block_of = [&](int64_t src, int b) {
-            while (src < begin[b]) --b;
-            while (src >= begin[b + 1]) ++b;
-            return b;
-        };
-        for (int64_t i = 0; i < n; ++i)
-            for (int64_t e = pr->row_ptr[i], b = 0; e < pr->row_ptr[i + 1]; ++e) {
-                b = block_of(pr->col[e], (int)b);
-                ++bptr[(size_t)b * (n + 1) + i + 1];
-            }
-        int64_t base = 0;
-        for (int b = 0; b < B; ++b) {
-            int64_t* p = bptr.data() + (size_t)b * (n + 1);
-            p[0] = base;
-            for (int64_t i = 0; i < n; ++i) p[i + 1] += p[i];
-            base = p[n];
-        }
-        std::vector<int64_t> pos(bptr);
-        std::vector<uint32_t> col2((size_t)std::max<int64_t>(nnz, 1));
-        std::vector<double> w2((size_t)std::max<int64_t>(nnz, 1));
-        for (int64_t i = 0; i < n; ++i)
-            for (int64_t e = pr->row_ptr[i], b = 0; e < pr->row_ptr[i + 1]; ++e) {
-                b = block_of(pr->col[e], (int)b);
-                const int64_t dst = pos[(size_t)b * (n + 1) + i]++;
-                col2[dst] = (uint32_t)pr->col[e];
-                w2[dst] = pr->weight[e];
-            }
-        if (csr_packed(n)) csr_sort_chunks(n, bptr, col2, w2);
-        csr_edges = 1;
-        for (int b = 0; b < B; ++b)
-            for (int64_t r0 = 0; r0 < n; r0 += csr_rows(n)) {
-                const int64_t* p = bptr.data() + (size_t)b * (n + 1);
-                const int64_t m = p[std::min<int64_t>(r0 + csr_rows(n), n)] - p[r0];
-                csr_edges = (int)std::min<int64_t>(kCsrChunk, std::max<int64_t>(csr_edges, m));
-            }
-        if ((s = alloc((void**)&d.row_ptr, (size_t)B * (n + 1) * 8))) return s;
-        if ((s = alloc((void**)&d.col, std::max<int64_t>(nnz, 1) * 4))) return s;
-        if ((s = alloc((void**)&d.w, std::max<int64_t>(nnz, 1) * kb))) return s;
-        if ((s = alloc((void**)&d.acc_part, (size_t)B * n * 8))) return s;
+        if ((s = kb == 8 ? upload_edges<double>(pr) : upload_edges<float>(pr))) return s;
+        if ((s = alloc((void**)&d.acc_part, (size_t)kCsrSourceBlocks * n * 8))) return s;
         if ((s = alloc((void**)&d.iapp, n * 8))) return s;
         for (int b = 0; b < 2; ++b)
             if ((s = alloc(&d.sx[b], n * kb))) return s;
-        HIPC(setup_copy(astream, (void*)d.row_ptr, bptr.data(), bptr.size() * 8));
-        if (nnz > 0) {
-            HIPC(setup_copy(astream, (void*)d.col, col2.data(), nnz * 4));
-            if (kb == 8) {
-                HIPC(setup_copy(astream, (void*)d.w, w2.data(), nnz * 8));
-            } else {
-                std::vector<float> wf(nnz);
-                for (int64_t e = 0; e < nnz; ++e) wf[e] = (float)w2[e];
-                HIPC(setup_copy(astream, (void*)d.w, wf.data(), nnz * 4));
-            }
-        }
         HIPC(setup_copy(astream, (void*)d.iapp, pr->per_elem, n * 8));
     }
     if (pr->topo == ND_LINKS) {
