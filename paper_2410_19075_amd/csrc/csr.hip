@@ -59,11 +59,10 @@ __device__ __forceinline__ T synapse(const double* p, double V) {
     return (T)1 / ((T)1 + exp(-((T)V - (T)p[8]) / (T)p[9]));
 }
 
-// The workgroup size BS is the most rows of a work item in the launch.  Networks of
-// 256 and of 512 rows share the launches of BS = 512; the sums do not depend on BS.
-// Six networks of 2000 to 2e5 neurons, us per step in two sets of launches, one after
-// the other / in one: degree 20 230 / 200, degree 100 538 / 554 (the 512-row items' LDS
-// holds back the smaller networks' workgroups).
+// The workgroup size BS is the most rows of a work item in the launch; the sums do not
+// depend on it.  Networks of 256 and of 512 rows in one batch share the launches of the
+// prologue and the update; their gathers are launched one after the other, each with its
+// own workgroup size, LDS and edges in flight (see Group::take).
 
 // Activations of the run's initial state (networks with g0 == 0).
 template <class KT, int BS>
@@ -86,7 +85,7 @@ __global__ __launch_bounds__(BS) void k_csr_prologue(const NetDesc* __restrict__
 // Phase A: synaptic partial sums of one source block for a tile of target rows.
 // Work item (row tile t, block x) is entry 8t + x; with the work map aligned
 // to multiples of 8 and the grid a multiple of 8, block x always lands on XCD x
-// (workgroups go to the XCDs round-robin), whose L2 then holds that block's
+// (workgroups go to the XCDs round-robin; w0 is a multiple of 8), whose L2 then holds that block's
 // slice of the activations.
 // The tile's in-edges of block x are one contiguous range of the block-major
 // edge arrays, cut into chunks of kCsrChunk edges.  Bound: with edges in row
@@ -102,12 +101,13 @@ __global__ __launch_bounds__(BS) void k_csr_prologue(const NetDesc* __restrict__
 // copy rate is 49 / 32 us; 1e6 neurons 458 / 346 us (560 / 558 us).
 template <class KT, int U, int BS>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_csr_gather(const NetDesc* __restrict__ D, const int2* __restrict__ work,
-                                                       const int* __restrict__ nwork_p, int stage, int j) {
+                                                       const int* __restrict__ nwork_p, int w0, int w1, int stage,
+                                                       int j) {
     extern __shared__ double prod[];  // the largest chunk of the group's networks
     __shared__ int64_t rb[BS + 1];
-    const int nwork = work_count(D, nwork_p);
+    const int nwork = min(w1, work_count(D, nwork_p));
     const int tid = threadIdx.x;
-    for (int w = blockIdx.x; w < nwork; w += gridDim.x) {
+    for (int w = w0 + (int)blockIdx.x; w < nwork; w += gridDim.x) {
         const int2 wk = work_at(work, w);
         const NetDesc& d = D[wk.x];
         if (j >= d.nsteps) continue;  // uniform over the block
@@ -274,16 +274,19 @@ hipError_t csr_launch_prologue(const CsrLaunch& L, int grid, hipStream_t s, NetD
     return hipGetLastError();
 }
 
-hipError_t csr_launch_stage(const CsrLaunch& L, int grid, int edges, hipStream_t s, NetDesc* D, const int2* work,
-                            const int* nwork, int stage, int j) {
+hipError_t csr_launch_gather(const CsrLaunch& L, int grid, int edges, hipStream_t s, NetDesc* D, const int2* work,
+                             const int* nwork, int w0, int w1, int stage, int j) {
     const size_t smem = (size_t)edges * sizeof(double);
     hipError_t e = hipSuccess;
     if (smem + (L.block + 1) * sizeof(int64_t) > 64 * 1024)
         e = hipFuncSetAttribute((const void*)L.gather, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(L.gather, dim3(grid), dim3(L.block), smem, s, D, work, nwork, stage, j);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(L.gather, dim3(grid), dim3(L.block), smem, s, D, work, nwork, w0, w1, stage, j);
+    return hipGetLastError();
+}
+
+hipError_t csr_launch_update(const CsrLaunch& L, int grid, hipStream_t s, NetDesc* D, const int2* work,
+                             const int* nwork, int stage, int j) {
     hipLaunchKernelGGL(L.update[stage - 1], dim3((grid + kSrcBlocks - 1) / kSrcBlocks), dim3(L.block), 0, s, D, work,
                        nwork, j);
     return hipGetLastError();

@@ -94,9 +94,11 @@ struct Net {
     // Networks of one kernel class share launches: model, topology, precision, tile,
     // tile_y, lattice (half-)width, ball workgroup size.  CSR networks of one precision
     // are one class whatever their rows per work item and edges in flight: their sums
-    // depend on neither, and the group takes one value of each (Group::take).
+    // depend on neither, and the group takes what each of its parts needs (Group::take).
     using Class = std::array<int, 7>;
     Class kernel_class() const;
+    // Part of its group: CSR networks by rows per work item (256: 0, 512: 1), others 0.
+    int part() const;
     nd_status prepare_observe(int64_t steps, const nd_observe* obs, bool may_alloc = true);
     NetDesc run_desc(double dt, int64_t steps) const;
     // chunked runs (serving): the run's step counter lives on the host and each
@@ -107,14 +109,21 @@ struct Net {
     NetDesc chunk_desc() const;
 };
 
+// CSR networks of one row count per work item in a group: they share gather launches.
+struct CsrPart {
+    int64_t items = 0;   // work items (0: no such network)
+    int edges = 0;       // edges of the largest chunk
+    int unroll = 0;      // edges in flight: of the network with the most links
+    int64_t nnz = 0;     // its links
+    bool mixed = false;  // the networks differ in edges in flight
+};
+
 // Networks of one kernel class launched together.
 struct Group {
     int model = 0, topo = 0, prec = 0, tile = 0;
-    int tile_y = 0, h = 0;  // cube: y tile extent, CSR: edges in flight; lattice (half-)width
-    int block = 0;          // ball, CSR: workgroup size
-    int edges = 0;          // CSR: edges of the largest chunk of its networks
-    int64_t nnz = 0;        // CSR: links of the network tile_y was taken from
-    bool mixed = false;     // CSR: its networks differ in tile_y
+    int tile_y = 0, h = 0;  // cube: y tile extent; lattice (half-)width
+    int block = 0;          // ball: workgroup size
+    CsrPart csr[2];         // CSR: the work items of part 0 precede those of part 1
     bool mv = false;        // some network records the mean phase velocity
     int ndesc = 0;
     int grid = 0;
@@ -201,7 +210,7 @@ hipError_t cube_launch_final(const CubeLaunch& L, int grid, hipStream_t s, NetDe
 // CSR kernels (csr.hip): work items of csr_rows target rows; `edges` bounds the
 // edges of every chunk (its products' LDS)
 struct CsrLaunch {
-    void (*gather)(const NetDesc*, const int2*, const int*, int, int);
+    void (*gather)(const NetDesc*, const int2*, const int*, int, int, int, int);
     void (*update[4])(const NetDesc*, const int2*, const int*, int);
     void (*prologue)(const NetDesc*, const int2*, const int*);
     int block;  // threads per workgroup: the most rows per work item in the launch
@@ -209,8 +218,11 @@ struct CsrLaunch {
 bool csr_select(int prec, int ept, int block, CsrLaunch* out);
 hipError_t csr_launch_prologue(const CsrLaunch& L, int grid, hipStream_t s, NetDesc* D, const int2* work,
                                const int* nwork);
-hipError_t csr_launch_stage(const CsrLaunch& L, int grid, int edges, hipStream_t s, NetDesc* D, const int2* work,
-                            const int* nwork, int stage, int j);
+// Work items w0 .. w1 - 1 (as far as there are any).
+hipError_t csr_launch_gather(const CsrLaunch& L, int grid, int edges, hipStream_t s, NetDesc* D, const int2* work,
+                             const int* nwork, int w0, int w1, int stage, int j);
+hipError_t csr_launch_update(const CsrLaunch& L, int grid, hipStream_t s, NetDesc* D, const int2* work,
+                             const int* nwork, int stage, int j);
 
 // Binary coupling matrices in the paper's compressed form (links.hip)
 struct LinksCompressed {

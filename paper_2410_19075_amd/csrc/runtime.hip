@@ -765,30 +765,34 @@ Net::Class Net::kernel_class() const {
 Group::Group(const Net::Class& c)
     : model(c[0]), topo(c[1]), prec(c[2]), tile(c[3]), tile_y(c[4]), h(c[5]), block(c[6]) {}
 
-// CSR: one set of launches for all, with the edges in flight of the network that has
-// the most links (see csr_unroll).  A set for each value, one after the other, takes
-// 129 us per step for 12 networks of 2000 neurons and degrees 5 to 100 (in one set
-// 51), 169 for 12 of 10^4 (114), 220 for four of 5 10^4 and degrees 10 to 100 (162).
+int Net::part() const { return prob.topo == ND_CSR && csr_rows(prob.n) > 256; }
+
+// CSR: one update launch for all, one gather launch for each row count, with the edges
+// in flight of its network that has the most links (see csr_unroll).  us per step of
+// batches in a set of launches for each row count and each value of edges in flight, one
+// after the other / so: 12 networks of 2000 neurons and degrees 5 to 100 127 / 59, 12 of
+// 10^4 168 / 113, four of 5 10^4 and degrees 10 to 100 220 / 161, six of 2000 to 10^5
+// neurons and degrees 10 to 100 316 / 222, of 2000 to 2 10^5 and degree 20 229 / 210.  (One
+// gather launch for both row counts: four of degree 100 beside 10^5 neurons of degree 10 take
+// 201 against 174 us, the LDS of the fullest items holds back the others' workgroups.)
 void Group::take(const Net& n) {
     mv = mv || n.mv_start >= 0;
     if (topo != ND_CSR) return;
-    edges = std::max(edges, n.csr_edges);
-    block = std::max(block, csr_rows(n.prob.n));
-    mixed = mixed || (tile_y && tile_y != n.cfg.tile_y);
-    if (!tile_y || n.prob.nnz > nnz) {
-        nnz = n.prob.nnz;
-        tile_y = n.cfg.tile_y;
+    CsrPart& c = csr[n.part()];
+    c.items += n.work_items();
+    c.edges = std::max(c.edges, n.csr_edges);
+    c.mixed = c.mixed || (c.unroll && c.unroll != n.cfg.tile_y);
+    if (!c.unroll || n.prob.nnz > c.nnz) {
+        c.nnz = n.prob.nnz;
+        c.unroll = n.cfg.tile_y;
     }
 }
 
-// Edges in flight of a CSR launch: 16 take twice the registers of 8, which halves the
-// waves of the lighter networks where the products' LDS would allow them, i.e. beside
+// Edges in flight of a gather launch: 16 take twice the registers of 8, which halves
+// the waves of the lighter networks where the products' LDS would allow them, i.e. of
 // 256-row work items (us per step with 16 / 8: 12 of 10^4 120 / 114, four of 5 10^4
-// 170 / 162; all of degree 100 148 / 148).  The LDS of 512-row items binds first
-// (2000 to 10^5 neurons, degrees 10 to 100: 227 / 235).
-static int csr_unroll(const Group& g) {
-    return g.mixed && g.block == 256 ? std::min(g.tile_y, 8) : g.tile_y;
-}
+// 170 / 162; all of degree 100 148 / 148).  The LDS of 512-row items binds first.
+static int csr_unroll(const CsrPart& c, int part) { return c.mixed && part == 0 ? std::min(c.unroll, 8) : c.unroll; }
 
 nd_status Net::prepare_observe(int64_t steps, const nd_observe* obs, bool may_alloc) {
     last_steps = steps;
@@ -932,14 +936,28 @@ nd_status enqueue_chunk(const Group& g, int chunk, hipStream_t st) {
         if ((e = links_launch_chunk(L, grid, st, g.desc, g.work, g.nwork, chunk, g.mv)) != hipSuccess)
             return hip_fail(e, "links chunk");
     } else {
-        CsrLaunch L;
-        if (!csr_select(g.prec, csr_unroll(g), g.block, &L))
-            return fail(ND_ERR_UNSUPPORTED, "no CSR kernel for %d edges per thread", csr_unroll(g));
-        if ((e = csr_launch_prologue(L, grid, st, g.desc, g.work, g.nwork)) != hipSuccess) return hip_fail(e, "csr prologue");
+        CsrLaunch L[2];
+        for (int p = 0; p < 2; ++p)
+            if (g.csr[p].items && !csr_select(g.prec, csr_unroll(g.csr[p], p), p ? 512 : 256, &L[p]))
+                return fail(ND_ERR_UNSUPPORTED, "no CSR kernel for %d edges per thread", csr_unroll(g.csr[p], p));
+        const CsrLaunch& all = L[g.csr[1].items ? 1 : 0];  // the larger workgroups
+        const bool both = g.csr[0].items && g.csr[1].items;
+        if ((e = csr_launch_prologue(all, grid, st, g.desc, g.work, g.nwork)) != hipSuccess) return hip_fail(e, "csr prologue");
         for (int j = 0; j < chunk; ++j)
-            for (int s = 1; s <= 4; ++s)
-                if ((e = csr_launch_stage(L, grid, g.edges, st, g.desc, g.work, g.nwork, s, j)) != hipSuccess)
-                    return hip_fail(e, "csr stage");
+            for (int s = 1; s <= 4; ++s) {
+                int w0 = 0;
+                for (int p = 0; p < 2; ++p) {
+                    if (!g.csr[p].items) continue;
+                    // (a part that is alone takes all items: in a captured chunk their number varies)
+                    const int m = both ? (int)g.csr[p].items : INT32_MAX;
+                    if ((e = csr_launch_gather(L[p], std::min(grid, m), g.csr[p].edges, st, g.desc, g.work, g.nwork, w0,
+                                               both ? w0 + m : m, s, j)) != hipSuccess)
+                        return hip_fail(e, "csr gather");
+                    w0 += m;
+                }
+                if ((e = csr_launch_update(all, grid, st, g.desc, g.work, g.nwork, s, j)) != hipSuccess)
+                    return hip_fail(e, "csr update");
+            }
     }
     hipLaunchKernelGGL(k_advance, dim3((g.ndesc + 255) / 256), dim3(256), 0, st, g.desc, g.ndesc, chunk);
     if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "advance");
@@ -1107,6 +1125,32 @@ nd_status staging_put(Staging* b, hipStream_t st) {
     }
     return ND_OK;
 }
+
+// Kernel classes of one call's networks.  CSR networks of both row counts share their
+// launches only while the edges of all stay in the Infinity Cache (256 MB) from stage to
+// stage; beyond, the smaller networks run their steps before the larger ones, each set
+// with more of its edges in the cache.  Six networks of 2000 to 2 10^5 neurons, us per
+// step together / one after the other: degree 20 (86 MB) 210 / 222, degree 50 (214 MB)
+// 356 / 302, degree 100 (428 MB) 543 / 524; 139 MB (eight of 2000 and one of 10^5, degree
+// 100) 175 / 181.
+class BatchClasses {
+public:
+    BatchClasses(Net* const* nets, int count, const int64_t* steps) {
+        for (int i = 0; i < count; ++i)
+            if (nets[i]->prob.topo == ND_CSR && steps[i] > 0)
+                edge_bytes_[fp64(nets[i])] += nets[i]->prob.nnz * (fp64(nets[i]) ? 12 : 8);
+    }
+    Net::Class of(const Net* n) const {
+        Net::Class c = n->kernel_class();
+        if (n->prob.topo == ND_CSR && edge_bytes_[fp64(n)] > kSharedBytes) c[6] = n->part();
+        return c;
+    }
+
+private:
+    static constexpr int64_t kSharedBytes = int64_t(192) << 20;
+    static bool fp64(const Net* n) { return n->prob.precision == ND_FP64; }
+    int64_t edge_bytes_[2] = {0, 0};
+};
 }  // namespace
 
 // Run a set of networks (possibly of different classes) for their own step
@@ -1135,11 +1179,14 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
     if (capturing(st))
         for (int i = 0; i < count; ++i) nets[i]->captured = true;
     // group by kernel class
+    const BatchClasses classes(nets, count, steps);
     std::map<Net::Class, std::vector<int>> groups;
     for (int i = 0; i < count; ++i)
-        if (steps[i] > 0) groups[nets[i]->kernel_class()].push_back(i);
+        if (steps[i] > 0) groups[classes.of(nets[i])].push_back(i);
     for (auto& kv : groups) {
-        const std::vector<int>& idx = kv.second;
+        std::vector<int>& idx = kv.second;
+        const Net* n0 = nets[idx[0]];
+        std::stable_partition(idx.begin(), idx.end(), [&](int q) { return nets[q]->part() == 0; });
         Group g(kv.first);
         g.ndesc = (int)idx.size();
         int64_t maxsteps = 0, nwork = 0;
@@ -1182,7 +1229,6 @@ nd_status run_nets(Net* const* nets, int count, const double* dt, const int64_t*
             g.work = (int2*)((char*)scratch + bd);
             g.nwork = (int*)((char*)scratch + bd + bw);
         }
-        const Net* n0 = nets[idx[0]];
         const int cfg_grid = n0->cfg.grid;
         g.grid = cfg_grid > 0 ? (int)std::min<int64_t>(cfg_grid, nwork) : (int)nwork;
         const int K = std::max(1, n0->cfg.chunk);
@@ -1323,13 +1369,14 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
     int* counts = (int*)(base + kNaDescBytes);
     int2* works = (int2*)(base + kNaDescBytes + kNaCountBytes);
     // groups of one kernel class, in order of first appearance
+    const BatchClasses classes(nets, count, steps);
     Net::Class key[ND_NOALLOC_MAX_NETS];
     int grp[ND_NOALLOC_MAX_NETS];
     int ngroups = 0;
     for (int i = 0; i < count; ++i) {
         grp[i] = -1;
         if (steps[i] == 0) continue;
-        const Net::Class k = nets[i]->kernel_class();
+        const Net::Class k = classes.of(nets[i]);
         int gi = 0;
         while (gi < ngroups && key[gi] != k) ++gi;
         if (gi == ngroups) key[ngroups++] = k;
@@ -1344,11 +1391,13 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
         g.work = works + wnext;
         g.nwork = counts + gi;
         int64_t maxsteps = 0, nwork = 0, values = 0;
-        int first = -1;
-        for (int i = 0; i < count; ++i) {
-            if (grp[i] != gi) continue;
-            if (first < 0) first = i;
+        const Net* n0 = nullptr;
+        for (int i = 0; i < count && !n0; ++i)
+            if (grp[i] == gi) n0 = nets[i];
+        for (int q = 0; q < 2 * count; ++q) {  // the networks of part 0, then those of part 1
+            const int i = q % count;
             const Net* n = nets[i];
+            if (grp[i] != gi || n->part() != q / count) continue;
             if ((e = put_desc(g.desc + g.ndesc, n->run_desc(dt[i], steps[i]), st)) != hipSuccess)
                 return hip_fail(e, "descriptor upload");
             ++g.ndesc;
@@ -1361,7 +1410,6 @@ static nd_status run_nets_noalloc(Net* const* nets, int count, const double* dt,
         if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "work map");
         dnext += g.ndesc;
         wnext += nwork;
-        const Net* n0 = nets[first];
         const int cfg_grid = n0->cfg.grid;
         g.grid = cfg_grid > 0 ? (int)std::min<int64_t>(cfg_grid, nwork) : (int)nwork;
         // the chunking of nd_run_batch: one chunk, or chunks of K steps where that

@@ -55,8 +55,12 @@ namespace nd {
     } while (0)
 
 // What a captured chunk depends on besides the class and its tables: mean-velocity
-// kernels; CSR: edges in flight, whether they differ, workgroup size, LDS.
-using ChunkShape = std::array<int, 5>;
+// kernels; CSR: edges in flight, whether they differ, LDS.
+using ChunkShape = std::array<int, 4>;
+
+// Requests of one key share chunks.  CSR requests by rows per work item, too: a chunk's
+// launches are captured for any number of work items, so only one part has its range.
+using ClassKey = std::pair<Net::Class, int>;
 
 struct Request {
     nd_req id = 0;
@@ -82,7 +86,7 @@ struct Request {
 };
 
 struct ClassTable {
-    Net::Class key;
+    ClassKey key;
     Group g;  // of the chunk being enqueued
     int cap_desc = 0, cap_work = 0;
     void* dev = nullptr;  // desc | work | nwork
@@ -97,7 +101,7 @@ struct ClassTable {
 
     // Start the group of a chunk, without networks.
     void reset_group() {
-        Group n(key);
+        Group n(key.first);
         n.ndesc = g.ndesc;
         n.grid = g.grid;
         n.desc = g.desc;
@@ -109,9 +113,13 @@ struct ClassTable {
     // serve all (320 steps of eight networks of 7000 neurons, degree 10 / 100: 14 / 29 ms;
     // with the LDS of the largest possible chunk 19 / 36 ms, two workgroups a CU).
     void round_group() {
-        if (g.topo == ND_CSR) g.edges = std::min(kCsrChunk, (g.edges + 511) / 512 * 512);
+        int& edges = g.csr[key.second].edges;
+        edges = std::min(kCsrChunk, (edges + 511) / 512 * 512);
     }
-    ChunkShape shape() const { return {g.mv, g.tile_y, g.mixed, g.block, g.edges}; }
+    ChunkShape shape() const {
+        const CsrPart& c = g.csr[key.second];
+        return {g.mv, c.unroll, c.mixed, c.edges};
+    }
     void drop_exec() {  // no chunk may be in flight
         for (auto& e : exec) (void)hipGraphExecDestroy(e.second);
         exec.clear();
@@ -260,7 +268,7 @@ nd_status Server::grow_work(ClassTable* t, int need) {
 }
 
 nd_status Server::table_for(Request* r, ClassTable** out) {
-    const Net::Class key = r->net->kernel_class();
+    const ClassKey key(r->net->kernel_class(), r->net->part());
     for (auto& t : classes)
         if (t->key == key) {
             *out = t.get();
@@ -270,7 +278,7 @@ nd_status Server::table_for(Request* r, ClassTable** out) {
     t->key = key;
     t->cap_desc = cfg.max_slots;
     t->slots.assign(cfg.max_slots, nullptr);
-    t->g = Group(key);
+    t->g = Group(key.first);
     t->g.ndesc = t->cap_desc;
     t->g.grid = cfg.grid;
     for (int b = 0; b < 2; ++b) {

@@ -312,16 +312,17 @@ def graph_nodes(torch, g):
 
 @pytest.mark.parametrize("prec", [0, 1])
 def test_hh_networks_of_all_degrees_and_sizes_share_launches(nd, prec):
-    """A batch of networks with every default of edges per thread and both row
-    counts per work item takes as many launches as one of equal networks, and gives
-    each network the bits of its run alone; so does an explicit value beside others."""
+    """A batch of networks with every default of edges per thread takes as many
+    launches as one of equal networks, with both row counts per work item one more
+    per stage, and gives each network the bits of its run alone; so does an explicit
+    value beside others."""
     import torch
     steps = 4
-    cases = [(700, 5), (66000, 40), (3000, 100), (1500, 60)]
+    cases = {"equal": [(700, 5)] * 4, "degrees": [(700, 5), (900, 40), (3000, 100), (1500, 60)],
+             "sizes": [(700, 5), (66000, 40), (3000, 100), (1500, 60)]}
     st = torch.cuda.Stream()
     nodes = {}
-    for kind in ("equal", "mixed"):
-        shapes = cases if kind == "mixed" else [cases[0]] * len(cases)
+    for kind, shapes in cases.items():
         hs, y0s, alone = [], [], []
         try:
             for n, deg in shapes:
@@ -354,7 +355,7 @@ def test_hh_networks_of_all_degrees_and_sizes_share_launches(nd, prec):
         finally:
             for h in hs:
                 nd.nd_destroy(h)
-    assert nodes["equal"] == nodes["mixed"], nodes
+    assert nodes["equal"] == nodes["degrees"] == nodes["sizes"] - 4 * steps, nodes
 
 
 @pytest.mark.parametrize("n, rows", [(65535, 256), (65536, 512)])
