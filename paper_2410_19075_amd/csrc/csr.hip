@@ -85,8 +85,8 @@ __global__ __launch_bounds__(BS) void k_csr_prologue(const NetDesc* __restrict__
 // Phase A: synaptic partial sums of one source block for a tile of target rows.
 // Work item (row tile t, block x) is entry 8t + x; with the work map aligned
 // to multiples of 8 and the grid a multiple of 8, block x always lands on XCD x
-// (workgroups go to the XCDs round-robin; w0 is a multiple of 8), whose L2 then holds that block's
-// slice of the activations.
+// (workgroups go to the XCDs round-robin; w0 is a multiple of 8), whose L2 then holds
+// that block's slice of the activations.
 // The tile's in-edges of block x are one contiguous range of the block-major
 // edge arrays, cut into chunks of kCsrChunk edges.  Bound: with edges in row
 // order every lane's gather is a request of its own to L2 (10 requests per clock
@@ -100,9 +100,9 @@ __global__ __launch_bounds__(BS) void k_csr_prologue(const NetDesc* __restrict__
 // 73 / 52 us (109 / 86 us in row order), of which the edge stream at the card's
 // copy rate is 49 / 32 us; 1e6 neurons 458 / 346 us (560 / 558 us).
 template <class KT, int U, int BS>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_csr_gather(const NetDesc* __restrict__ D, const int2* __restrict__ work,
-                                                       const int* __restrict__ nwork_p, int w0, int w1, int stage,
-                                                       int j) {
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_csr_gather(
+    const NetDesc* __restrict__ D, const int2* __restrict__ work, const int* __restrict__ nwork_p, int w0, int w1,
+    int stage, int j) {
     extern __shared__ double prod[];  // the largest chunk of the group's networks
     __shared__ int64_t rb[BS + 1];
     const int nwork = min(w1, work_count(D, nwork_p));

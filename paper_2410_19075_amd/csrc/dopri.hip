@@ -59,7 +59,7 @@ struct DenseOut {
     int64_t y_stride;
 };
 
-// Bound: FP64 issue, 7 stages of the resident RK4 kernel's work and 34 coefficient
+// Bound: FP64 issue, six stages of the resident RK4 kernel's work and 34 coefficient
 // FMAs per element and accepted step.  Measured per attempt (rings of 1024, one /
 // 512): Kuramoto 8.3 / 19 us, FHN 6.9 / 14.6 us; with four barriers per stage, the
 // prefix completed in LDS and branches on the wrap 14.1 / 25.6 and 12.9 / 26.7 us.
@@ -326,7 +326,7 @@ __global__ __launch_bounds__(kDpBS) __attribute__((amdgpu_waves_per_eu(4))) void
 // Bound: launches and their latency up to some 10^5 elements, HBM beyond, the rows'
 // gathers for matrices.  Per attempt, against a map launch and an RHS launch per
 // stage: FHN ring of 65,536 90 -> 69 us, of 10^6 361 -> 307 us, four Kuramoto rings of
-// 65,536 132 -> 107 us; 60^3 inertia matrix network (65 links a row) with its outputs
+// 65,536 132 -> 107 us; 60^3 inertia matrix network (33 links a row) with its outputs
 // 4.22 -> 2.74 ms a run to t = 50, its tiles of 512 -> 256 and the outputs' slopes read
 // once included.
 constexpr int kDtBS = 256;

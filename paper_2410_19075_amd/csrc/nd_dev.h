@@ -19,9 +19,10 @@ __host__ __device__ constexpr int csr_rows(int64_t n) { return n < (int64_t(1) <
 constexpr int kCsrSlotBits = 13;    // CSR: bits of an edge's place inside its chunk
 constexpr int kCsrChunk = 1 << kCsrSlotBits;  // CSR: edges whose products are in LDS at once
 // Edges are stored as (source - block begin) << kCsrSlotBits | slot where that
-// fits 32 bits, sorted by source inside each chunk; in larger networks (where a
-// chunk holds less than one edge per eight cache lines of its block, so that
-// sorting gains nothing) as the source alone, in row order.
+// fits 32 bits, sorted by source inside each chunk; in larger networks as the
+// source alone, in row order.  There a block's activations are 32768 or more cache
+// lines in FP64, 16384 in FP32-bulk, for the 8192 edges of a chunk at the most, so
+// neighbouring lanes of a sorted chunk would seldom read the same line.
 __host__ __device__ constexpr bool csr_packed(int64_t n) {
     return (n + kCsrSourceBlocks - 1) / kCsrSourceBlocks <= (int64_t(1) << (32 - kCsrSlotBits));
 }

@@ -27,10 +27,12 @@
 // streams, longest class first onto the stream with the least work, and joins
 // before the status copies and the chunk's end event, which therefore cover every
 // class.  Chunk k + 1 forks behind the join of chunk k, so buffers, tables and
-// staging are used in the same order as on one stream.  Four streams in all: the
-// device gives a process four hardware queues.  Measured on 24 ring requests of
-// 2^10 to 2^16 elements and 300 to 1000 steps (nine classes): 49 ms, 90 ms with the
-// classes one after the other.
+// staging are used in the same order as on one stream.  Four streams run chunks: the
+// device gives a process four hardware queues, and the copy stream, which is a
+// fifth, shares one of them with a chunk's stream while it uploads or downloads.
+// Measured on 24 ring requests of 2^10 to 2^16 elements and 300 to 1000 steps (nine
+// classes): 48 to 55 ms, by which queues the streams share; 90 ms with the classes
+// one after the other.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
