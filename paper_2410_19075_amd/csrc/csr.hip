@@ -97,8 +97,8 @@ __global__ __launch_bounds__(BS) void k_csr_prologue(const NetDesc* __restrict__
 // LDS at that slot, and the owner thread of each row adds its row's products in
 // row order, so the sums do not depend on the sorting, on U or on the chunking.
 // Measured per stage with the update (FP64 / FP32-bulk, degree 100): 2e5 neurons
-// 73 / 52 us (109 / 86 us in row order), of which the edge stream at the card's
-// copy rate is 49 / 32 us; 1e6 neurons 458 / 346 us (560 / 558 us).
+// 71 / 49 us (109 / 86 us in row order), of which the edge stream at the card's
+// copy rate is 49 / 32 us; 1e6 neurons 443 / 343 us (560 / 558 us).
 template <class KT, int U, int BS>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_csr_gather(
     const NetDesc* __restrict__ D, const int2* __restrict__ work, const int* __restrict__ nwork_p, int w0, int w1,
@@ -127,6 +127,12 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
         __syncthreads();
         const int64_t E0 = rb[0], E1 = rb[nrows];
         const int64_t mb = tid < nrows ? rb[tid] : E1, me = tid < nrows ? rb[tid + 1] : E1;
+        // rb is rewritten by the next work item, and an item without edges passes no
+        // barrier in the chunk loop: one stands behind these reads, or behind the item
+        // (us per stage with the update, 1e6 neurons of degree 100: FP64 458 / 443,
+        // FP32-bulk 343 / 372)
+        constexpr bool kEarlyBarrier = sizeof(KT) == 4;
+        if constexpr (kEarlyBarrier) lds_barrier();
         double a = 0.0;
         for (int64_t c0 = E0; c0 < E1; c0 += kCsrChunk) {
             const int m = (int)min((int64_t)kCsrChunk, E1 - c0);
@@ -168,9 +174,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(4))) void k_
             __syncthreads();
         }
         if (tid < nrows) gp(d.acc_part)[(int64_t)x * n + r0 + tid] = a;
-        // rb is rewritten by the next work item, and an item without edges has passed
-        // no barrier since its row bounds were read
-        lds_barrier();
+        if constexpr (!kEarlyBarrier) lds_barrier();
     }
 }
 
