@@ -667,10 +667,11 @@ def main_adaptive(nd, torch, args, stream):
             what = (f"Kuramoto-Sakaguchi with inertia, 3D lattice {args.n}^3 periodic, ball of radius 2 (33 links) "
                     f"as a compressed coupling matrix, m=1 eps=0.05 mu=0.01 alpha=0.45, planted coherent ball, psi=0")
     else:
-        # algorithmic FP64 flops per element and accepted step: 7 stages of the resident
-        # kernel's per-stage work (KURAMOTO_RESIDENT_FLOPS / 4 each, sin/cos included)
-        # plus the stage combinations (2 flops per coefficient, 27 + 7 coefficients)
-        flops = acc * n * (7 * KURAMOTO_RESIDENT_FLOPS / 4 + 2 * 34)
+        # algorithmic FP64 flops per element and accepted step: six slopes (the seventh
+        # stage's is the next step's first) of the resident kernel's per-stage work
+        # (KURAMOTO_RESIDENT_FLOPS / 4 each, sin/cos included) plus the stage
+        # combinations (2 flops per coefficient, 27 + 7 coefficients)
+        flops = acc * n * (6 * KURAMOTO_RESIDENT_FLOPS / 4 + 2 * 34)
         achieved = flops / ev_total / 1e12
         roof = {"bound": "alu", "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": achieved / FP64_PEAK_TFLOPS, "traffic": None, "kernel": "k_ring_dopri<Kuramoto>"}

@@ -386,3 +386,31 @@ def test_hh_config_reports_the_rows_that_run(nd, n, rows):
                 nd.nd_set_config(h, c)
     finally:
         nd.nd_destroy(h)
+
+
+def test_hh_batch_of_both_sizes_beyond_the_cache(nd):
+    """Networks of both row counts whose edges together exceed what shares launches
+    (192 MB): each has the bits of its run alone, in both kinds of batch run."""
+    shapes = [(30000, 120), (70000, 200), (500, 30)]
+    rng = np.random.default_rng(5)
+    hs, y0s, alone = [], [], []
+    print("case hh batch beyond the cache", flush=True)
+    try:
+        for n, deg in shapes:
+            g = (np.arange(n + 1, dtype=np.int64) * deg,
+                 np.sort(rng.integers(0, n, size=(n, deg), dtype=np.int32), axis=1).ravel(), rng.random(n * deg) * 0.1)
+            y, p, y0, _ = run_net(nd, n, g, 3)
+            alone.append(y)
+            y0s.append(y0)
+            hs.append(nd.nd_create(p))
+        for run in (nd.nd_run_batch, nd.nd_run_batch_noalloc):
+            for h, y0 in zip(hs, y0s):
+                nd.nd_set_state(h, y0, on_device=0)
+            run(hs, [0.01] * len(hs), [3] * len(hs))
+            for h, y in zip(hs, alone):
+                got = np.empty_like(y)
+                nd.nd_get_state(h, got, on_device=0)
+                assert np.array_equal(got, y)
+    finally:
+        for h in hs:
+            nd.nd_destroy(h)
