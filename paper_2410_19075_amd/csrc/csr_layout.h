@@ -125,15 +125,18 @@ CsrLayout<KT> csr_layout(int64_t n, const int64_t* row_ptr, const int32_t* col, 
     }
     L.edges = (int)std::min<int64_t>(kCsrChunk, std::max<int64_t>(1, widest));
     CsrChunkSort sort(n, L.edges);
-    std::vector<uint32_t> tc((size_t)B * widest);
-    std::vector<KT> tw((size_t)B * widest);
+    int64_t fullest = 0;  // edges of the fullest row tile
+    for (int64_t r0 = 0; r0 < n; r0 += rows) fullest = std::max(fullest, row_ptr[std::min(r0 + rows, n)] - row_ptr[r0]);
+    std::vector<uint32_t> tc(fullest);
+    std::vector<KT> tw(fullest);
     for (int64_t r0 = 0; r0 < n; r0 += rows) {
         const int64_t r1 = std::min(r0 + rows, n);
         uint32_t* pc[B];
         KT* pw[B];
-        for (int b = 0; b < B; ++b) {
-            pc[b] = tc.data() + b * widest;
-            pw[b] = tw.data() + b * widest;
+        for (int64_t b = 0, o = 0; b < B; ++b) {
+            pc[b] = tc.data() + o;
+            pw[b] = tw.data() + o;
+            o += L.bptr[(size_t)b * (n + 1) + r1] - L.bptr[(size_t)b * (n + 1) + r0];
         }
         for (int64_t i = r0; i < r1; ++i) {
             const int32_t* c = col + row_ptr[i];
@@ -164,11 +167,11 @@ CsrLayout<KT> csr_layout(int64_t n, const int64_t* row_ptr, const int32_t* col, 
         }
         for (int b = 0; b < B; ++b) {
             const int64_t* p = L.bptr.data() + (size_t)b * (n + 1);
-            const uint32_t* sc = tc.data() + b * widest;
-            const KT* sw = tw.data() + b * widest;
+            const int64_t m = p[r1] - p[r0];
+            const uint32_t* sc = pc[b] - m;  // (advanced to the end above)
+            const KT* sw = pw[b] - m;
             uint32_t* dc = L.col.get() + p[r0];
             KT* dw = L.w.get() + p[r0];
-            const int64_t m = p[r1] - p[r0];
             if (!packed) {
                 std::copy(sc, sc + m, dc);
                 std::copy(sw, sw + m, dw);
